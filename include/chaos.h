@@ -15,7 +15,9 @@
  *    work is enqueued on `stream` and is asynchronous: the caller
  *    synchronises (hipStreamSynchronize / torch.cuda.synchronize) before it
  *    reads results.  stream = NULL means the null stream.
- *  - One call at a time per chaos_net; different nets are independent.
+ *  - One call at a time per chaos_net, its device work included (calls of one
+ *    net that overlap on different streams race on the net's workspace);
+ *    different nets are independent.
  *  - Images are fp32, row-major [n][in_h * in_w]; labels int32 in
  *    [0, n_classes) where n_classes is the output size of the last layer.
  *    Labels live in device memory and are not range-checked: a label
@@ -111,11 +113,13 @@ int chaos_set_params(chaos_net *net, const float *src_dev, hipStream_t stream);
  *   grad_sum_dev   [n_params]      sum_i dE_i/dW, accumulated in a fixed
  *                                  order: bitwise reproducible run to run
  *   grad_each_dev  [n][n_params]   per-sample gradients
- * n = 0 writes zeros into grad_sum_dev and nothing else.  A gradient sum
- * uses net-owned partial sums allocated on first use (grown when a call
- * needs more); for the large net without grad_each_dev also 47.6 KB per
- * sample of per-sample operands, whose conv3 and FC1 weight gradients are
- * then contracted over the batch (CHAOS_ENOMEM if they cannot be had). */
+ * n = 0 writes zeros into grad_sum_dev and nothing else.  Gradients use
+ * net-owned workspace allocated on first use (grown when a call needs more,
+ * CHAOS_ENOMEM if it cannot be had): for the batched engine at most about
+ * 1 GiB, beyond which the samples go through it in several passes.  Outputs
+ * and losses of a call without gradients are those of a training pass at
+ * lr = 0 bit for bit; one with gradients sums in another order and agrees to
+ * fp32 rounding. */
 int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *labels_dev,
                            int64_t n, float *out_dev, float *loss_dev, float *grad_sum_dev,
                            float *grad_each_dev, hipStream_t stream);
@@ -123,20 +127,19 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation and outputs as chaos_forward_backward, with no hipMalloc,
- * hipFree or other allocating call.  A gradient sum keeps its per-worker
- * partial sums in a fixed 32 MiB array of device memory that the library
- * holds on every device it runs on until the process ends, instead of
- * net-owned buffers allocated on first use; it therefore runs at most
- * 32 MiB / (4 n_params) workers (small net 512, medium 110, large 23) and
- * the large net's conv3 and FC1 gradients are pushed per sample rather than
- * contracted over the batch.  The sum is bitwise reproducible from call to
+ * hipFree or other allocating call.  The workspace is what the net allocated
+ * when it was created, and a gradient sum's partial sums are in a fixed 32 MiB
+ * array of device memory that the library holds on every device it runs on
+ * until the process ends; so the samples go through the batched engine in more
+ * passes and with fewer rows of partial sums than chaos_forward_backward's (a
+ * net that the engine does not serve runs at most 32 MiB / (4 n_params)
+ * workers).  The sum is bitwise reproducible from call to
  * call; it equals chaos_forward_backward's to rounding (a different fixed
  * order), outputs and losses are identical.  A net with more than 8,388,608
  * weights cannot take a gradient sum here (CHAOS_EUNSUPPORTED).  Every call
  * on one device shares that array: calls that overlap in time on one device
  * (different streams, threads or nets) race and give wrong sums; calls
- * ordered on one stream are safe.  The array is cleared by a kernel at the
- * start of each call (no memset node when captured). */
+ * ordered on one stream are safe.  No memset node is recorded when captured. */
 int chaos_forward_backward_noalloc(chaos_net *net, const float *x_dev, const int32_t *labels_dev,
                                    int64_t n, float *out_dev, float *loss_dev, float *grad_sum_dev,
                                    float *grad_each_dev, hipStream_t stream);

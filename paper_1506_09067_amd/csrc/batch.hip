@@ -1,0 +1,2038 @@
+// Batched frozen-weight engine: the forward pass of many samples at fixed
+// weights (Validation and Testing, Section III-A.1), layer by layer instead of
+// sample by sample, for any net whose first layer is a convolution.
+//
+// Every layer is a matrix product over (sample, position) rows.  The first
+// layer (one input map, raw pixels) runs on the fp32 matrix instructions.
+// The others run on the bf16 ones, sixteen times their rate: an fp32 operand
+// is split without loss into three bf16 terms (x = h + m + l, 8 significant
+// bits each, rounded to nearest), and the six products hh, hm, mh, hl, lh, mm
+// are accumulated in fp32; the three left out are below 2^-25 of |a||b|.
+// Measured against float64 sums of 160 to 2176 products (gfx950, 16x16x32):
+// relative error 1.8e-7 to 7.3e-7, fp32 matrix instructions 2.3e-7 to 8.4e-7.
+//
+// Activations are fp32 in memory, [sample][position][map], so that eight
+// channels of one position are one operand fragment.  A workgroup stages its
+// samples' inputs in LDS, split once, and gathers its rows from there by
+// position; the weights are split and laid out in fragment order by a kernel
+// at the start of each call (they may have changed since the last one).
+#include "batch.h"
+#include "device_common.h"
+
+#include <algorithm>
+
+namespace chaos {
+namespace {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+// eight bf16 of an operand fragment, kept as four words: the register
+// allocator takes vectors of 16-bit elements apart
+typedef int frag __attribute__((ext_vector_type(4)));
+
+constexpr int NT_ = 256;  // threads of a workgroup: four wavefronts
+constexpr int kLds = 160 * 1024;
+constexpr int kCus = 256;
+
+__device__ __forceinline__ f4 mfma_bf(frag a, frag b, f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ uint32_t fdiv(uint32_t i, FastDiv f) { return f.d == 1 ? i : __umulhi(i, f.m); }
+
+FastDiv fast_div(int d) { return FastDiv{d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d), (uint32_t)d}; }
+
+// x = h + m + l exactly (barring underflow); an infinite or NaN x keeps its
+// value in h alone
+__device__ __forceinline__ void split8(const float (&v)[8], frag &h, frag &m, frag &l) {
+    bf8 hv, mv, lv;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const __bf16 a = (__bf16)v[j];
+        const float r = v[j] - (float)a;
+        const __bf16 b = (__bf16)r;
+        hv[j] = a;
+        mv[j] = b;
+        lv[j] = (__bf16)(r - (float)b);
+    }
+    h = __builtin_bit_cast(frag, hv);
+    m = __builtin_bit_cast(frag, mv);
+    l = __builtin_bit_cast(frag, lv);
+}
+
+// eight channels 8 c8 .. of one position's C, zero past C
+__device__ __forceinline__ void load8(const float *__restrict__ row, int c8, int C, bool vec, float (&v)[8]) {
+    const int c = 8 * c8;
+    if (vec) {  // C % 4 == 0 and 16-byte aligned rows
+        const f4 a = *(const f4 *)(row + c);
+        const f4 b = (c + 4 < C) ? *(const f4 *)(row + c + 4) : f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[j] = a[j]; v[4 + j] = b[j]; }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = (c + j < C) ? row[c + j] : 0.0f;
+    }
+}
+
+// ---- weights into fragment order ---------------------------------------------
+// Forward, column tile ct, K step ks: lane l holds map o = 16 ct + l % 16 at the
+// eight channels of chunk q = 4 ks + l / 16, chunk (kernel position, 8 channels).
+// Backward data, row tile rt, K step ks: lane l holds the eight maps of chunk
+// 4 ks + l / 16 for row i = l % 16: input 16 rt + i of a fully connected layer;
+// else kernel position 4 tg + i % 4 of input map 4 cq + i / 4, rt = (tg, cq).
+struct PackDesc {
+    int first;  // first work item of this pack
+    int back;
+    int w_off, w_stride;
+    int C, C8, T, O, KS, CQ, flat, prevP;
+    FastDiv fKS, fC8, fC, fCQ;
+    int64_t dst;
+};
+struct PackArgs {
+    const float *params;
+    uint16_t *pack;
+    int n_desc, items;
+    PackDesc d[2 * kMaxLayers];
+};
+
+// canonical index within one map's weights of (channel, kernel position)
+__device__ __forceinline__ int weight_index(int flat, int c, int tap, int T, int prevP, FastDiv fC) {
+    if (!flat) return c * T + tap;
+    // flattened input (position, map) of the layer below: maps come first in
+    // the canonical order
+    const int pos = fdiv(c, fC);
+    return (c - pos * (int)fC.d) * prevP + pos;
+}
+
+__global__ void __launch_bounds__(NT_) pack_kernel(PackArgs a) {
+    const int t = blockIdx.x * NT_ + threadIdx.x;
+    if (t >= a.items) return;
+    int k = 0;
+    while (k + 1 < a.n_desc && t >= a.d[k + 1].first) ++k;
+    const PackDesc &d = a.d[k];
+    const int e = t - d.first, lane = e & 63, tk = e >> 6;
+    const int ct = fdiv(tk, d.fKS), ks = tk - ct * d.KS;
+    const int i = lane & 15, q = 4 * ks + (lane >> 4);
+    float v[8];
+    if (!d.back) {
+        const int o = 16 * ct + i, tap = fdiv(q, d.fC8), c0 = 8 * (q - tap * d.C8);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int c = c0 + j;
+            const bool ok = o < d.O && tap < d.T && c < d.C;
+            v[j] = ok ? a.params[d.w_off + o * d.w_stride + weight_index(d.flat, c, tap, d.T, d.prevP, d.fC)] : 0.0f;
+            if (!(ks & 1)) v[j] = -v[j];  // even K steps are subtracted
+        }
+    } else {
+        const int tg = fdiv(ct, d.fCQ), cq = ct - tg * d.CQ;
+        const int c = d.flat ? 16 * ct + i : 4 * cq + (i >> 2), tap = d.flat ? 0 : 4 * tg + (i & 3);
+        const bool ok = c < d.C && tap < d.T;
+        const int w = ok ? weight_index(d.flat, c, tap, d.T, d.prevP, d.fC) : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int o = 8 * q + j;
+            v[j] = (ok && o < d.O) ? a.params[d.w_off + o * d.w_stride + w] : 0.0f;
+        }
+    }
+    frag h, m, l;
+    split8(v, h, m, l);
+    frag *dst = (frag *)(a.pack + d.dst) + (int64_t)tk * 192 + lane;
+    dst[0] = h;
+    dst[64] = m;
+    dst[128] = l;
+}
+
+// ---- pooling ----------------------------------------------------------------
+// How a layer's outputs leave its accumulators:
+//   1  no pooling: every element is activated and stored
+//   2  2x2 windows: rows are ordered (pooled position, window element), so a
+//      lane's four accumulator elements are one window
+//   0  any window: the pre-activation map goes through LDS
+// f is strictly increasing and the bias is the window's own, so both are applied
+// to the window's maximum alone (a comparison after the bias was added would
+// round every element once more); the first maximum wins.
+__device__ __forceinline__ float pool_window(const float *z, int zs, int Wo, int p, float bias, int &arg) {
+    float m = z[0];
+    arg = 0;
+    for (int u = 0; u < p; ++u)
+        for (int v = 0; v < p; ++v) {
+            const float c = z[(u * Wo + v) * zs];
+            if (c > m) { m = c; arg = u * p + v; }
+        }
+    return m + bias;
+}
+
+// position (sample s, y, x) of row r under the row order of POOL
+struct RowDiv {
+    int P, Wo, Pp, Wp;
+    FastDiv fP, fWo, fPp, fWp;
+};
+template <int POOL>
+__device__ __forceinline__ void row_position(const RowDiv &d, int r, int &s, int &y, int &x) {
+    if constexpr (POOL == 2) {
+        const int P = r >> 2, w = r & 3;
+        s = fdiv(P, d.fPp);
+        const int pp = P - s * d.Pp, py = fdiv(pp, d.fWp);
+        y = 2 * py + (w >> 1);
+        x = 2 * (pp - py * d.Wp) + (w & 1);
+    } else {
+        s = fdiv(r, d.fP);
+        const int pp = r - s * d.P;
+        y = fdiv(pp, d.fWo);
+        x = pp - y * d.Wo;
+    }
+}
+
+// The outputs of one 16x16 tile (rows row0 + 4 lg + r, map o) for POOL 1 and 2:
+// dst points at the workgroup's first sample, rows are its valid rows.
+template <int POOL>
+__device__ __forceinline__ void store_tile(f4 t, int row0, int lg, int rows, int o, bool ok, int O, float bias,
+                                           float *__restrict__ y, uint8_t *__restrict__ arg) {
+    if constexpr (POOL == 2) {
+        float m = t[0];
+        int ag = 0;
+#pragma unroll
+        for (int r = 1; r < 4; ++r)
+            if (t[r] > m) { m = t[r]; ag = r; }
+        const float ym = act_y(m + bias);
+        const int P = (row0 >> 2) + lg;
+        if (ok && 4 * P < rows) {
+            y[P * O + o] = ym;
+            if (arg) arg[P * O + o] = (uint8_t)ag;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = row0 + 4 * lg + r;
+            const float v = act_y(t[r] + bias);
+            if (ok && row < rows) y[row * O + o] = v;
+        }
+    }
+}
+
+// The outputs of the workgroup's pre-activation map z [row][on] in LDS, maps
+// o0 .. o0 + on.
+__device__ __forceinline__ void store_map(const float *z, int ns, int on, FastDiv fon, int o0, const RowDiv &d, int p,
+                                          int O, const float *__restrict__ bias, float *__restrict__ y,
+                                          uint8_t *__restrict__ arg) {
+    const int items = ns * d.Pp * on;
+    for (int t = threadIdx.x; t < items; t += NT_) {
+        const int sp = fdiv(t, fon), o = t - sp * on;
+        const int s = fdiv(sp, d.fPp), P = sp - s * d.Pp, py = fdiv(P, d.fWp), px = P - py * d.Wp;
+        int ag;
+        const float m = pool_window(z + (s * d.P + py * p * d.Wo + px * p) * on + o, on, d.Wo, p, bias[o0 + o], ag);
+        y[sp * O + o0 + o] = act_y(m);
+        if (arg) arg[sp * O + o0 + o] = (uint8_t)ag;
+    }
+}
+
+// ---- first layer -----------------------------------------------------------
+// y = pool(f(b + W * x)) of the one-map input, S samples a workgroup, on the
+// fp32 16x16x4 instruction (the raw pixels may be anything): rows are
+// positions, columns maps, K the kernel.  Little arithmetic, so what counts is
+// that a workgroup is small (images and weights, 5 KB of LDS) and many are
+// resident to cover each other's loads.
+struct FirstArgs {
+    const float *x, *params;
+    float *y;
+    uint8_t *arg;
+    int64_t n;
+    int S, HW, W, K, KK, KS;      // KS: K steps of 4
+    int O, OP, p, nout;
+    int w_off, w_stride, b_off;
+    int z_off, w_lds, k_lds;      // LDS offsets in floats
+    RowDiv d;
+    FastDiv fK, fO, fOP;
+};
+
+template <int POOL, int NT>
+__global__ void __launch_bounds__(NT_) conv_first_kernel(FirstArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lg = lane >> 4;
+    const int64_t s0 = (int64_t)blockIdx.x * a.S;
+    const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S);
+    float *xs = lds, *wl = lds + a.w_lds, *z = lds + a.z_off;
+    int *koff = (int *)(lds + a.k_lds);
+    {
+        // images and weights requested together
+        const float *xg = a.x + s0 * a.HW;
+        const int nx = ns * a.HW, nw = 4 * a.KS * a.OP;
+        constexpr int U = 4;
+        for (int i0 = tid; i0 < (nx > nw ? nx : nw); i0 += U * NT_) {
+            float v[U], w[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_, k = fdiv(i, a.fOP), o = i - k * a.OP;
+                v[q] = i < nx ? xg[i] : 0.0f;
+                w[q] = (i < nw && k < a.KK && o < a.O) ? a.params[a.w_off + o * a.w_stride + k] : 0.0f;
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_;
+                if (i < nx) xs[i] = v[q];
+                if (i < nw) wl[i] = w[q];
+            }
+        }
+    }
+    for (int k = tid; k < 4 * a.KS; k += NT_) {
+        const int u = fdiv(k, a.fK);
+        koff[k] = (k < a.KK) ? u * a.W + (k - u * a.K) : -1;
+    }
+    __syncthreads();
+    constexpr int MT = 4;
+    const int rows = ns * a.d.P, RG = (rows + 16 * MT - 1) / (16 * MT), CG = (a.OP + 16 * NT - 1) / (16 * NT);
+    for (int job = wave; job < RG * CG; job += 4) {
+        const int cg = job / RG, rg = job - cg * RG;
+        f4 acc[MT][NT];
+        int base[MT];
+        float bias[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int o = 16 * (NT * cg + j) + lr;
+            bias[j] = a.params[a.b_off + (o < a.O ? o : 0)];
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int r = 16 * (MT * rg + i) + lr;
+            int s, y, x;
+            row_position<POOL>(a.d, r < rows ? r : 0, s, y, x);
+            base[i] = s * a.HW + y * a.W + x;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int ks = 0; ks < a.KS; ++ks) {
+            const int k = 4 * ks + lg, ko = koff[k];
+            float av[MT], bv[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int o = 16 * (NT * cg + j) + lr;
+                bv[j] = wl[k * a.OP + (o < a.OP ? o : 0)];
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                av[i] = xs[base[i] + (ko >= 0 ? ko : 0)];
+                if (ko < 0) av[i] = 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = mfma(av[i], bv[j], acc[i][j]);
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int o = 16 * (NT * cg + j) + lr;
+            if (16 * (NT * cg + j) >= a.O) continue;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int row0 = 16 * (MT * rg + i);
+                if constexpr (POOL == 1) {
+                    store_tile<POOL>(acc[i][j], row0, lg, rows, o, o < a.O, a.O, bias[j], a.y + s0 * a.nout, nullptr);
+                } else if constexpr (POOL == 2) {
+                    // the window's maximum and its element, activated below
+                    float m = acc[i][j][0];
+                    int ag = 0;
+#pragma unroll
+                    for (int r = 1; r < 4; ++r)
+                        if (acc[i][j][r] > m) { m = acc[i][j][r]; ag = r; }
+                    const int P = (row0 >> 2) + lg;
+                    if (o < a.O && 4 * P < rows) {
+                        z[P * a.O + o] = m + bias[j];
+                        if (a.arg) a.arg[s0 * a.nout + P * a.O + o] = (uint8_t)ag;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = row0 + 4 * lg + r;
+                        if (row < rows && o < a.O) z[row * a.O + o] = acc[i][j][r];
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (POOL == 0) {
+        __syncthreads();
+        store_map(z, ns, a.O, a.fO, 0, a.d, a.p, a.O, a.params + a.b_off, a.y + s0 * a.nout,
+                  a.arg ? a.arg + s0 * a.nout : nullptr);
+    } else if constexpr (POOL == 2) {
+        // every lane on an output: a tile's 16 columns hold 5 to 20 maps
+        __syncthreads();
+        for (int t = tid; t < ns * a.nout; t += NT_) a.y[s0 * a.nout + t] = act_y(z[t]);
+    }
+}
+
+// ---- the other layers -------------------------------------------------------
+// Rows: (sample, position) of S samples; columns: maps; K: (kernel position,
+// channel) in steps of 32.  A wavefront's job is MT x NT tiles of 16x16.
+//   WK = 1  the jobs are spread over the four wavefronts
+//   WK = 4  every wavefront takes a quarter of each job's K (layers with a long
+//           K and few rows); the quarters are added in a fixed order through LDS
+// WK depends on the layer alone and the tiling has no part in the order of a
+// sum, so an output's bits do not depend on how many samples a call has.
+struct FwdArgs {
+    const float *in, *bias;
+    const uint16_t *pack;
+    float *y;
+    uint8_t *arg;
+    int64_t n;
+    int S, HW, W, C, C8, st, K, T, vec;
+    int O, p, nout;
+    int KS, CT, ctb;               // K steps, column tiles, column tiles per workgroup
+    int tab, red, z, alias;        // LDS offsets in bytes; alias: red and z overlay the inputs
+    RowDiv d;
+    FastDiv fC8, fK, fon, fon_last;  // maps of a workgroup, of the last one
+};
+
+template <int MT, int NT, int WK, int POOL>
+__global__ void __launch_bounds__(NT_, 1) conv_fwd_kernel(FwdArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s0 = (int64_t)blockIdx.x * a.S;
+    const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S);
+    int *tab = (int *)(smem + a.tab);  // byte offset of chunk q from a row's position
+    for (int q = tid; q < 4 * a.KS; q += NT_) {
+        const int t = fdiv(q, a.fC8), c8 = q - t * a.C8, u = fdiv(t, a.fK);
+        tab[q] = (t < a.T) ? (u * a.W + (t - u * a.K)) * a.st + c8 * 48 : 0;
+    }
+    {
+        const float *src = a.in + s0 * a.HW * a.C;
+        const int items = ns * a.HW * a.C8;
+        constexpr int U = 8;  // positions in flight per thread
+        for (int i0 = tid; i0 < items; i0 += U * NT_) {
+            float v[U][8];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_, ic = i < items ? i : i0, pos = fdiv(ic, a.fC8);
+                load8(src + (int64_t)pos * a.C, ic - pos * a.C8, a.C, a.vec, v[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_, pos = fdiv(i, a.fC8);
+                if (i < items) {
+                    frag h, m, l;
+                    split8(v[q], h, m, l);
+                    frag *dst = (frag *)(smem + pos * a.st + (i - pos * a.C8) * 48);
+                    dst[0] = h;
+                    dst[1] = m;
+                    dst[2] = l;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int ctile0 = blockIdx.y * a.ctb, ctn = (a.CT - ctile0 < a.ctb) ? a.CT - ctile0 : a.ctb;
+    const int o0 = 16 * ctile0, on = (a.O - o0 < 16 * ctn) ? a.O - o0 : 16 * ctn;  // this workgroup's maps
+    const int rows = ns * a.d.P, RG = (rows + 16 * MT - 1) / (16 * MT), CG = (ctn + NT - 1) / NT;
+    float *z = (float *)(smem + a.z);
+    const int kper = (WK == 1) ? a.KS : (a.KS + 3) / 4;
+    const int k0 = (WK == 1) ? 0 : wave * kper, k1 = (k0 + kper < a.KS) ? k0 + kper : a.KS;
+    const int jobs = RG * CG;
+    float *yg = a.y + s0 * a.nout + o0;
+    uint8_t *ag = a.arg ? a.arg + s0 * a.nout + o0 : nullptr;
+    // (with alias there is one job per wavefront, and every wavefront passes the
+    // barriers once; without, the barriers of WK = 4 are in a uniform loop)
+    for (int job = (WK == 1) ? wave : 0; job < jobs || a.alias; job += (WK == 1) ? 4 : 1) {
+        const int cg = job / RG, rg = job - cg * RG;
+        f4 acc[MT][NT];
+        if (job < jobs) {
+            int base[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int r = 16 * (MT * rg + i) + lr;
+                int s, y, x;
+                row_position<POOL>(a.d, r < rows ? r : 0, s, y, x);
+                base[i] = (s * a.HW + y * a.W + x) * a.st;
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+            // weights: a wavefront-uniform base and the lane's 16 bytes
+            const frag *bp[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int ct = ctile0 + NT * cg + j;
+                bp[j] = (const frag *)a.pack + (int64_t)(ct < a.CT ? ct : a.CT - 1) * a.KS * 192;
+            }
+            auto load_a = [&](frag (&f)[3], int i, int off) {
+                const frag *src = (const frag *)(smem + base[i] + off);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) f[q] = src[q];
+            };
+            auto load_b = [&](frag (&f)[NT][3], int ks) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) f[j][q] = bp[j][ks * 192 + 64 * q + lane];
+            };
+            // One K step, G row tiles at a time: the six products of the step,
+            // smallest first, are summed from zero by the matrix core and the
+            // sum is added to the accumulator by the vector unit, which rounds
+            // to nearest (the matrix core rounds down: a chain of six roundings
+            // per step against the full sum costs four times the error, and the
+            // weights of even steps are packed negated and subtracted, so that
+            // what offset is left cancels).  Then these tiles' operands of the next step are read in
+            // the place of this one's; the next step's weights arrive in a
+            // second buffer meanwhile.
+            constexpr int G = (NT >= 4) ? 1 : (NT >= 2) ? 2 : (MT < 4 ? MT : 4);
+            static_assert(MT % G == 0, "whole groups of row tiles");
+            frag av[MT][3], bA[NT][3], bB[NT][3];
+            auto step = [&](const frag (&fb)[NT][3], int off, float sign) {
+                constexpr int ta[6] = {0, 2, 1, 0, 1, 0}, tb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+                for (int i0 = 0; i0 < MT; i0 += G) {
+                    f4 t[G][NT];
+#pragma unroll
+                    for (int q = 0; q < 6; ++q)
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j)
+                                t[g][j] = mfma_bf(av[i0 + g][ta[q]], fb[j][tb[q]], q ? t[g][j] : f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int g = 0; g < G; ++g) load_a(av[i0 + g], i0 + g, off);
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                acc[i0 + g][j][r] = fmaf(t[g][j][r], sign, acc[i0 + g][j][r]);
+                }
+            };
+            const float sign0 = (k0 & 1) ? 1.0f : -1.0f;
+            if (k0 < k1) {
+                const int off0 = tab[4 * k0 + lg];
+                load_b(bA, k0);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) load_a(av[i], i, off0);
+            }
+            // (the step past the last one reads the last one's operands again)
+            for (int ks = k0; ks < k1; ks += 2) {
+                const int n1 = ks + 1 < k1 ? ks + 1 : ks, n2 = ks + 2 < k1 ? ks + 2 : n1;
+                const int o1 = tab[4 * n1 + lg], o2 = tab[4 * n2 + lg];
+                load_b(bB, n1);
+                __builtin_amdgcn_sched_barrier(0);
+                step(bA, o1, sign0);
+                if (ks + 1 < k1) {
+                    load_b(bA, n2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    step(bB, o2, -sign0);
+                }
+            }
+        }
+        auto leave = [&](f4 t, int i, int j) {  // tile (i, j) of the job
+            const int o = 16 * (NT * cg + j) + lr, row0 = 16 * (MT * rg + i);
+            if constexpr (POOL) {
+                store_tile<POOL>(t, row0, lg, rows, o, o < on, a.O, a.bias[o0 + (o < on ? o : 0)], yg, ag);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = row0 + 4 * lg + r;
+                    if (row < rows && o < on) z[row * on + o] = t[r];
+                }
+            }
+        };
+        if constexpr (WK == 1) {
+            if (POOL == 0 && a.alias) __syncthreads();
+            if (job < jobs) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    if (16 * (NT * cg + j) >= on) continue;
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) leave(acc[i][j], i, j);
+                }
+            }
+        } else {
+            // (w0 + w2) + (w1 + w3)
+            float *red = (float *)(smem + a.red);
+            __syncthreads();
+            if (wave >= 2) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        *(f4 *)(red + (((wave - 2) * MT * NT + i * NT + j) * 64 + lane) * 4) = acc[i][j];
+            }
+            __syncthreads();
+            if (wave < 2) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) {
+                        f4 *slot = (f4 *)(red + ((wave * MT * NT + i * NT + j) * 64 + lane) * 4);
+                        *slot = acc[i][j] + *slot;
+                    }
+            }
+            __syncthreads();
+#pragma unroll 4
+            for (int t = wave; t < MT * NT; t += 4) {
+                const int i = t / NT, j = t - i * NT;
+                leave(*(const f4 *)(red + (t * 64 + lane) * 4) +
+                          *(const f4 *)(red + ((MT * NT + t) * 64 + lane) * 4),
+                      i, j);
+            }
+        }
+        if (a.alias) break;
+    }
+    if constexpr (POOL == 0) {
+        __syncthreads();
+        store_map(z, ns, on, (int)blockIdx.y == (int)gridDim.y - 1 ? a.fon_last : a.fon, o0, a.d, a.p, a.O, a.bias, yg - o0,
+                  ag ? ag - o0 : nullptr);
+    }
+}
+
+// ---- outputs, loss, wrong count -----------------------------------------------
+struct LossArgs {
+    const float *y;  // last layer's outputs [n][P][C]
+    const int32_t *labels;
+    int64_t n;
+    int C, P;
+    float *out, *loss;
+    float *e;  // dE/dy, laid out as y, or null
+    int32_t *n_wrong;
+};
+
+__global__ void __launch_bounds__(NT_) loss_kernel(LossArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * NT_ + threadIdx.x;
+    const int no = a.C * a.P;
+    bool wrong = false;
+    if (i < a.n) {
+        const float *y = a.y + i * no;
+        const int label = a.labels[i];
+        float best = y[0], sum = 0.0f;
+        int arg = 0;
+        for (int c = 0; c < a.C; ++c)  // canonical order: maps, then positions
+            for (int q = 0; q < a.P; ++q) {
+                const int k = c * a.P + q;
+                const float v = y[q * a.C + c];
+                if (a.out) a.out[i * no + k] = v;
+                if (v > best) { best = v; arg = k; }
+                const float d = v - (k == label ? 1.0f : 0.0f);
+                if (a.e) a.e[i * no + q * a.C + c] = d;
+                sum = fmaf(d, d, sum);
+            }
+        if (a.loss) a.loss[i] = 0.5f * sum;
+        wrong = arg != label;
+    }
+    if (a.n_wrong) {
+        const unsigned long long m = __ballot(wrong);
+        if ((threadIdx.x & 63) == 0 && m) atomicAdd(a.n_wrong, __popcll(m));
+    }
+}
+
+// ---- backward --------------------------------------------------------------
+// A layer's output deltas d = dE/dy f'(z) of positions (s, y, x), eight maps at
+// a time, split into LDS [position][8 maps][plane]: f' from y, and zero at every
+// element of a pooling window but its recorded maximum.
+struct DeltaArgs {
+    const float *e, *y;  // [sample][pooled position][O]
+    const uint8_t *arg;
+    int O, vec, p, Wo, Wp, Pp;
+    FastDiv fp;
+};
+
+// The bf16 matrix instruction rounds towards minus infinity: one value is off
+// by a fraction of an ulp, but a sum of many (a gradient over all positions) by
+// the same fraction each, four times the error of fp32 instructions (measured).
+// So every other column (backward data) or K step (weight gradients) is computed
+// for the negated deltas and its result negated back, and the offsets cancel.
+
+// e and y of eight maps from o = 8 o8, and the recorded maximum
+struct Delta8 {
+    float e[8], y[8];
+    int arg[8], w;
+};
+__device__ __forceinline__ void delta_load(const DeltaArgs &d, int64_t s, int y, int x, int o8, Delta8 &v) {
+    int pp, w = 0;
+    if (d.p == 1) {
+        pp = y * d.Wo + x;
+    } else {
+        const int py = fdiv(y, d.fp), px = fdiv(x, d.fp);
+        pp = py * d.Wp + px;
+        w = (y - py * d.p) * d.p + (x - px * d.p);
+    }
+    const int64_t row = (s * d.Pp + pp) * d.O;
+    load8(d.e + row, o8, d.O, d.vec, v.e);
+    load8(d.y + row, o8, d.O, d.vec, v.y);
+    v.w = w;
+    if (d.p > 1) {
+        const uint8_t *ar = d.arg + row + 8 * o8;
+        if (d.vec) {
+            const uint32_t lo = *(const uint32_t *)ar, hi = (8 * o8 + 4 < d.O) ? *(const uint32_t *)(ar + 4) : 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v.arg[j] = (lo >> (8 * j)) & 255;
+                v.arg[4 + j] = (hi >> (8 * j)) & 255;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v.arg[j] = (8 * o8 + j < d.O) ? ar[j] : 0;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v.arg[j] = 0;
+    }
+}
+__device__ __forceinline__ void delta_store(const Delta8 &v, char *dst, bool negate) {
+    float t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float d = (v.arg[j] == v.w) ? v.e[j] * dact_from_y(v.y[j]) : 0.0f;
+        t[j] = negate ? -d : d;
+    }
+    frag h, m, l;
+    split8(t, h, m, l);
+    frag *q = (frag *)dst;
+    q[0] = h;
+    q[1] = m;
+    q[2] = l;
+}
+
+// ---- backward data, convolutions -----------------------------------------------
+// dE/d(input): C[(kernel position, map)][position] = sum_o W[o][..] d[o][position]
+// as a matrix product, then col2im into the input errors in LDS.  A workgroup
+// holds S samples' errors of one block of input maps; the positions go through
+// in chunks of 16 NT.  Row tiles hold four kernel positions of four maps (lane
+// group = map, accumulator element = kernel position), so the lanes of one
+// scatter instruction never meet; two wavefronts never work on one quad of maps
+// at a time (quads in turn, a barrier per round unless each wavefront keeps to
+// its own quads), so sums have a fixed order.
+struct BackArgs {
+    DeltaArgs d;
+    const uint16_t *pack;
+    float *out;        // [sample][position][C]
+    int64_t n;
+    int S, HW, W, C, CQ, T, TG, K, KS, O8, ost;
+    int qb, qp;        // quads of maps per workgroup, and padded to the wavefronts
+    int ES;            // floats per position of the errors in LDS
+    int d_off, sink;   // LDS offsets in bytes
+    RowDiv r;
+    FastDiv fO8, fqp, fK, fES;
+};
+
+// KSR > 0: the deltas' fragments of all K steps are kept in registers (short
+// K); 0: read from LDS for each row tile.
+template <int MT, int NT, int NWV, int KSR>
+__global__ void __launch_bounds__(64 * NWV, KSR ? 2 : 1) conv_back_kernel(BackArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    constexpr int TH = 64 * NWV;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s0 = (int64_t)blockIdx.x * a.S;
+    const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S);
+    const int q0 = blockIdx.y * a.qb, qn = (a.CQ - q0 < a.qb) ? a.CQ - q0 : a.qb;
+    float *err = (float *)smem;
+    char *ds = smem + a.d_off;
+    float *sink = (float *)(smem + a.sink) + lane;
+    for (int i = tid; i < ns * a.HW * a.ES; i += TH) err[i] = 0.0f;
+    const int cols = ns * a.r.P, tgm = (a.TG + MT - 1) / MT;
+    const int jobs = tgm * a.qp;
+    const bool own = a.qp % NWV == 0;  // every wavefront keeps to its own quads
+    for (int col0 = 0; col0 < cols; col0 += 16 * NT) {
+        if (col0) __syncthreads();
+        {
+            const int items = 16 * NT * a.O8;
+            constexpr int U = 4;
+            for (int i0 = tid; i0 < items; i0 += U * TH) {
+                Delta8 v[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = i0 + q * TH, p = fdiv(i, a.fO8), col = col0 + p;
+                    int s, y, x;
+                    row_position<1>(a.r, (i < items && col < cols) ? col : 0, s, y, x);
+                    delta_load(a.d, s0 + s, y, x, i < items ? i - p * a.O8 : 0, v[q]);
+                    if (col >= cols) v[q].w = -1;  // columns past the last position: zero
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = i0 + q * TH, p = fdiv(i, a.fO8);
+                    if (i < items) delta_store(v[q], ds + p * a.ost + (i - p * a.O8) * 48, p & 1);
+                }
+            }
+        }
+        __syncthreads();
+        // this lane's column in each tile
+        int eb[NT];
+        bool cv[NT];
+        const char *bcol[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int col = col0 + 16 * j + lr;
+            int s, y, x;
+            cv[j] = col < cols;
+            row_position<1>(a.r, cv[j] ? col : 0, s, y, x);
+            eb[j] = (s * a.HW + y * a.W + x) * a.ES + lg;
+            bcol[j] = ds + (16 * j + lr) * a.ost;
+        }
+        auto load_b = [&](frag (&f)[3], int j, int ks) {
+            // a chunk past O8 meets zero weights; it reads the column's first
+            const int ch = 4 * ks + lg;
+            const frag *src = (const frag *)(bcol[j] + (ch < a.O8 ? ch : 0) * 48);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) f[q] = src[q];
+        };
+        constexpr int ta[6] = {0, 2, 1, 0, 1, 0}, tb[6] = {2, 0, 1, 1, 0, 0};
+        frag breg[KSR ? KSR : 1][KSR ? NT : 1][3];
+        if constexpr (KSR > 0) {
+#pragma unroll
+            for (int ks = 0; ks < KSR; ++ks)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) load_b(breg[ks][j], j, ks);
+        }
+        auto load_a = [&](frag (&f)[MT][3], int tg0, int cq, int ks) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int tg = tg0 + i < a.TG ? tg0 + i : a.TG - 1;
+                const frag *src = (const frag *)a.pack + ((int64_t)(tg * a.CQ + q0 + cq) * a.KS + ks) * 192;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) f[i][q] = src[64 * q + lane];
+            }
+        };
+        for (int j0 = 0; j0 < jobs; j0 += NWV) {
+            const int job = j0 + wave;
+            const int tq = fdiv(job, a.fqp), cq = job - tq * a.qp, tg0 = MT * tq;
+            if (job < jobs && cq < qn) {
+                f4 acc[MT][NT];
+                if constexpr (KSR > 0) {
+                    frag av[KSR][MT][3];
+#pragma unroll
+                    for (int ks = 0; ks < KSR; ++ks) load_a(av[ks], tg0, cq, ks < a.KS ? ks : 0);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KSR; ++ks) {
+                        if (ks < a.KS) {
+                            f4 t[MT][NT];
+#pragma unroll
+                            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                                    for (int j = 0; j < NT; ++j)
+                                        t[i][j] = mfma_bf(av[ks][i][ta[q]], breg[ks][j][tb[q]],
+                                                          q ? t[i][j] : f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                                for (int j = 0; j < NT; ++j) acc[i][j] += t[i][j];
+                        }
+                    }
+                } else {
+                    frag aA[MT][3], aB[MT][3];
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+                    auto step = [&](const frag (&av)[MT][3], int ks) {
+                        frag bv[2][3];
+                        load_b(bv[0], 0, ks);
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) {
+                            if (j + 1 < NT) load_b(bv[(j + 1) & 1], j + 1, ks);
+                            f4 t[MT];
+#pragma unroll
+                            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                                for (int i = 0; i < MT; ++i)
+                                    t[i] = mfma_bf(av[i][ta[q]], bv[j & 1][tb[q]], q ? t[i] : f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                            for (int i = 0; i < MT; ++i) acc[i][j] += t[i];
+                        }
+                    };
+                    load_a(aA, tg0, cq, 0);
+                    for (int ks = 0; ks < a.KS; ks += 2) {
+                        if (ks + 1 < a.KS) load_a(aB, tg0, cq, ks + 1);
+                        step(aA, ks);
+                        if (ks + 1 < a.KS) {
+                            if (ks + 2 < a.KS) load_a(aA, tg0, cq, ks + 2);
+                            step(aB, ks + 1);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int tap = 4 * (tg0 + i) + r;
+                        if (tap >= a.T) continue;
+                        const int u = fdiv(tap, a.fK), off = (u * a.W + tap - u * a.K) * a.ES + 4 * cq;
+                        float *p[NT];
+                        float c[NT];
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) {
+                            p[j] = cv[j] ? err + eb[j] + off : sink;
+                            c[j] = (lr & 1) ? -acc[i][j][r] : acc[i][j][r];
+                        }
+                        scatter_add<NT>(p, 0, c);
+                    }
+            }
+            if (!own) __syncthreads();
+        }
+    }
+    __syncthreads();
+    // the block's maps of every position
+    for (int i = tid; i < ns * a.HW * a.ES; i += TH) {
+        const int pos = fdiv(i, a.fES), c = i - pos * a.ES;
+        if (c < 4 * qn && 4 * q0 + c < a.C) a.out[(s0 * a.HW + pos) * a.C + 4 * q0 + c] = err[i];
+    }
+}
+
+// ---- backward data, fully connected layers ----------------------------------------
+// dE/d(input)[i] of 64 samples a workgroup: rows i (16 a tile), columns samples.
+struct FlatArgs {
+    DeltaArgs d;
+    const uint16_t *pack;
+    float *out;
+    int64_t n;
+    int C, RT, KS, O8, ost, vec_out;
+    FastDiv fO8;
+};
+
+__global__ void __launch_bounds__(512, 1) flat_back_kernel(FlatArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    constexpr int TH = 512, NT = 4, MT = 2;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s0 = (int64_t)blockIdx.x * 16 * NT;
+    const int ns = (int)((a.n - s0 < 16 * NT) ? a.n - s0 : 16 * NT);
+    const int items = 16 * NT * a.O8;
+    for (int i = tid; i < items; i += TH) {
+        const int s = fdiv(i, a.fO8);
+        Delta8 v;
+        delta_load(a.d, s0 + (s < ns ? s : 0), 0, 0, i - s * a.O8, v);
+        if (s >= ns) v.w = -1;
+        delta_store(v, smem + s * a.ost + (i - s * a.O8) * 48, s & 1);
+    }
+    __syncthreads();
+    constexpr int ta[6] = {0, 2, 1, 0, 1, 0}, tb[6] = {2, 0, 1, 1, 0, 0};
+    for (int t0 = MT * (blockIdx.y * 8 + wave); t0 < a.RT; t0 += MT * 8 * gridDim.y) {
+        f4 acc[MT][NT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        auto load_a = [&](frag (&f)[MT][3], int ks) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int rt = t0 + i < a.RT ? t0 + i : a.RT - 1;
+                const frag *src = (const frag *)a.pack + ((int64_t)rt * a.KS + ks) * 192;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) f[i][q] = src[64 * q + lane];
+            }
+        };
+        auto step = [&](const frag (&av)[MT][3], int ks) {
+            const int ch = 4 * ks + lg;
+            frag bv[NT][3];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const frag *src = (const frag *)(smem + (16 * j + lr) * a.ost + (ch < a.O8 ? ch : 0) * 48);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) bv[j][q] = src[q];
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                f4 t[NT];
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        t[j] = mfma_bf(av[i][ta[q]], bv[j][tb[q]], q ? t[j] : f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] += t[j];
+            }
+        };
+        frag aA[MT][3], aB[MT][3];
+        load_a(aA, 0);
+        for (int ks = 0; ks < a.KS; ks += 2) {
+            if (ks + 1 < a.KS) load_a(aB, ks + 1);
+            step(aA, ks);
+            if (ks + 1 < a.KS) {
+                if (ks + 2 < a.KS) load_a(aA, ks + 2);
+                step(aB, ks + 1);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int c = 16 * (t0 + i) + 4 * lg;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int s = 16 * j + lr;
+                if (s >= ns || t0 + i >= a.RT) continue;
+                float *dst = a.out + (s0 + s) * a.C + c;
+                const f4 v = (lr & 1) ? -acc[i][j] : acc[i][j];
+                if (a.vec_out && c + 4 <= a.C) {
+                    *(f4 *)dst = v;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (c + r < a.C) dst[r] = v[r];
+                }
+            }
+        }
+    }
+}
+
+// ---- weight gradients ----------------------------------------------------------
+// G[o][(kernel position, map)] = sum over samples and positions of d * input: rows
+// are maps o, columns quads of input maps under one kernel position, K the
+// positions of a unit (S samples, or a band of output rows of one sample).  Both
+// operands run along the positions while LDS holds them by position, eight maps
+// together: the LDS transpose read (ds_read_b64_tr_b16: lane i of sixteen gives
+// the address of four elements of row i / 4 and gets one column of the four
+// rows) makes fragments of either, each row at an address of its own, which is
+// what the im2col gather needs.  One more column holds ones: the bias gradient.
+// Accumulators stay in registers over a chunk of units; every chunk leaves one
+// row of partial sums, added in order afterwards.
+struct WgradArgs {
+    DeltaArgs d;
+    const float *in;
+    float *part;
+    int64_t n, units;          // units of all samples of this pass
+    int64_t upc;               // units per chunk
+    int S, NB, RB;             // samples per unit, bands per sample, output rows per band
+    int im2col, vec_in;
+    int C, W, K, T, inrows;    // input rows staged per sample
+    int Ho, O;
+    int NCQ, C8s, sts;         // quads of maps per workgroup; chunks and bytes per staged position
+    int o8s, osts;             // the same of the deltas
+    int tgs, ctw, kw;          // column subgroups, column tiles per wavefront, wavefronts along K
+    int CQ, RTT;               // quads of maps, row tiles
+    int tab, in_off, d_off, cst;  // LDS offsets in bytes; cst: the ones, then a zero row
+    int accumulate, npmax;
+    int64_t rowsize;           // floats of a partial row of this layer
+    RowDiv r;                  // positions of a unit: P = RB Wo
+    FastDiv fC8s, fo8s, fNCQ, fW, fK, ftgs, fHWs;
+    // per-sample gradients instead of partial sums
+    float *each;
+    int64_t each_stride;
+};
+
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s4v lds_s4v;
+
+// canonical gradient index of (map o, local quad q, map e of the quad) or -1
+struct WgradIndex {
+    int C, T, NCQ, CQ, O, cw_off, cb_off, rowlen, flat, prevP, wT;
+    FastDiv fNCQ, fprev;
+};
+__device__ __forceinline__ int wgrad_index(const WgradIndex &d, int o, int cqg, int q, int e) {
+    if (o >= d.O) return -1;
+    if (q == d.T * d.NCQ) return (cqg == 0 && e == 0) ? d.cb_off + o : -1;
+    const int tap = fdiv(q, d.fNCQ), c = 4 * (cqg * d.NCQ + q - tap * d.NCQ) + e;
+    if (tap >= d.T || c >= d.C) return -1;
+    return d.cw_off + o * d.rowlen + weight_index(d.flat, c, tap, d.wT, d.prevP, d.fprev);
+}
+
+template <int RTM, int CTM, int WR>
+__global__ void __launch_bounds__(256 * WR, WR == 1 ? 2 : 1) conv_wgrad_kernel(WgradArgs a, WgradIndex ix) {
+    extern __shared__ __align__(16) char smem[];
+    constexpr int TH = 256 * WR;
+    const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, w4 = wave & 3;
+    const int WC = 4 / a.kw, wc = w4 % WC, wk = w4 / WC;
+    const int cqg = fdiv(blockIdx.y, a.ftgs), tsub = blockIdx.y - cqg * a.tgs;
+    const int cq0 = cqg * a.NCQ;
+    const int rt0 = (blockIdx.z * WR + wr) * RTM;          // this wavefront's first row tile
+    const int rtn = (a.RTT - rt0 < RTM) ? a.RTT - rt0 : RTM;  // may be <= 0
+    const int zt0 = blockIdx.z * WR * RTM;                 // the workgroup's first row tile
+    const int64_t u0 = blockIdx.x * a.upc, u1 = (u0 + a.upc < a.units) ? u0 + a.upc : a.units;
+    if (u0 >= u1) return;
+    int *tab = (int *)(smem + a.tab);
+    for (int p = tid; p < a.npmax; p += TH) {
+        int s, y, x;
+        row_position<1>(a.r, p, s, y, x);
+        const bool in = p < a.S * a.r.P;
+        tab[p] = !in ? 0 : a.im2col ? p * a.sts : (s * a.inrows * a.W + y * a.W + x) * a.sts;
+    }
+    for (int i = tid; i < (48 + a.osts + 96) / 4; i += TH) ((int *)(smem + a.cst))[i] = 0;
+    __syncthreads();
+    if (tid == 0) *(__bf16 *)(smem + a.cst) = (__bf16)1.0f;
+    // this wavefront's columns
+    const int tile0 = tsub * WC * a.ctw + wc * a.ctw, nq = a.T * a.NCQ;
+    int qoff[CTM];
+    bool one[CTM];
+#pragma unroll
+    for (int j = 0; j < CTM; ++j) {
+        const int q = 4 * (tile0 + j) + (i16 & 3), tap = fdiv(q, a.fNCQ), cl = q - tap * a.NCQ;
+        const int u = fdiv(tap, a.fK);
+        one[j] = q == nq;
+        qoff[j] = (q < nq) ? (u * a.W + tap - u * a.K) * a.sts + (cl >> 1) * 48 + (cl & 1) * 8 : 0;
+    }
+    const int64_t prow = (int64_t)blockIdx.x * a.kw + wk;
+    auto slot = [&](int i, int j) {
+        return a.part + prow * a.rowsize +
+               (((int64_t)(blockIdx.y * WC + wc) * a.ctw + j) * a.RTT + rt0 + i) * 256 + lane * 4;
+    };
+    f4 acc[RTM][CTM];
+#pragma unroll
+    for (int i = 0; i < RTM; ++i)
+#pragma unroll
+        for (int j = 0; j < CTM; ++j) {
+            acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+            if (a.accumulate && i < rtn && j < a.ctw) acc[i][j] = *(const f4 *)slot(i, j);
+        }
+    const int drow = 96 * (rt0 - zt0) + ((i16 & 3) >> 1) * 48 + (i16 & 1) * 8;
+    for (int64_t u = u0; u < u1; ++u) {
+        const int64_t sg = u / a.NB;
+        const int b = (int)(u - sg * a.NB), y0 = b * a.RB;
+        const int64_t s0 = sg * a.S;
+        const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S);
+        const int rb = (a.Ho - y0 < a.RB) ? a.Ho - y0 : a.RB;
+        const int npos = (ns - 1) * a.r.P + rb * a.r.Wo;
+        __syncthreads();  // the previous unit's operands have been read
+        {
+            const int items = npos * a.o8s;
+            constexpr int U = 2;
+            for (int i0 = tid; i0 < items; i0 += U * TH) {
+                Delta8 v[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = (i0 + q * TH < items) ? i0 + q * TH : i0, p = fdiv(i, a.fo8s);
+                    int s, y, x;
+                    row_position<1>(a.r, p, s, y, x);
+                    const int o8 = 2 * zt0 + i - p * a.o8s;
+                    delta_load(a.d, s0 + s, y0 + y, x, 8 * o8 < a.O ? o8 : 0, v[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = i0 + q * TH, p = fdiv(i, a.fo8s);
+                    if (i < items) delta_store(v[q], smem + a.d_off + p * a.osts + (i - p * a.o8s) * 48, ((p >> 5) + u) & 1);
+                }
+            }
+        }
+        if (!a.im2col) {
+            const int rows = rb + a.K - 1;
+            const int per = a.inrows * a.W;  // staged positions per sample
+            const int items = ((ns - 1) * per + rows * a.W) * a.C8s;
+            constexpr int U = 4;
+            for (int i0 = tid; i0 < items; i0 += U * TH) {
+                float v[U][8];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = (i0 + q * TH < items) ? i0 + q * TH : i0, pos = fdiv(i, a.fC8s), c8 = i - pos * a.C8s;
+                    const int s = fdiv(pos, a.fHWs), pp = pos - s * per;
+                    const int c = 4 * cq0 + 8 * c8;
+                    const float *row = a.in + ((s0 + s) * (int64_t)(a.Ho + a.K - 1) * a.W + (int64_t)y0 * a.W + pp) * a.C;
+                    if (c < a.C) {
+                        if (a.vec_in) {
+                            const f4 lo = *(const f4 *)(row + c);
+                            const f4 hi = (c + 4 < a.C) ? *(const f4 *)(row + c + 4) : f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) { v[q][j] = lo[j]; v[q][4 + j] = hi[j]; }
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) v[q][j] = (c + j < a.C) ? row[c + j] : 0.0f;
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) v[q][j] = 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int i = i0 + q * TH, pos = fdiv(i, a.fC8s);
+                    if (i < items) {
+                        frag h, m, l;
+                        split8(v[q], h, m, l);
+                        frag *dst = (frag *)(smem + a.in_off + pos * a.sts + (i - pos * a.C8s) * 48);
+                        dst[0] = h;
+                        dst[1] = m;
+                        dst[2] = l;
+                    }
+                }
+            }
+        } else {
+            // the first layer: the kernel's pixels under each output position
+            const int items = npos * a.C8s, inW = a.W;
+            for (int i = tid; i < items; i += TH) {
+                const int p = fdiv(i, a.fC8s), c8 = i - p * a.C8s;
+                int s, y, x;
+                row_position<1>(a.r, p, s, y, x);
+                const float *img = a.in + (s0 + s) * (int64_t)(a.Ho + a.K - 1) * inW + (y0 + y) * inW + x;
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int k = 4 * cq0 + 8 * c8 + j, uu = fdiv(k, a.fK);
+                    v[j] = (k < a.C) ? img[uu * inW + k - uu * a.K] : 0.0f;
+                }
+                frag h, m, l;
+                split8(v, h, m, l);
+                frag *dst = (frag *)(smem + a.in_off + p * a.sts + c8 * 48);
+                dst[0] = h;
+                dst[1] = m;
+                dst[2] = l;
+            }
+        }
+        __syncthreads();
+        auto tr = [&](int addr) {  // one plane's fragment half
+            return __builtin_bit_cast(uint64_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v *)(smem + addr)));
+        };
+        const int nks = (npos + 31) / 32;
+        for (int ks = wk; ks < nks; ks += a.kw) {
+            const float sign = ((ks + u) & 1) ? -1.0f : 1.0f;
+            int pd[2], pi[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int p = 32 * ks + 8 * lg + 4 * h + (i16 >> 2);
+                pi[h] = a.in_off + (p < npos ? tab[p] : 0);  // a staged position: its product with the zero row is zero
+                pd[h] = (p < npos ? a.d_off + p * a.osts : a.cst + 48) + drow;
+            }
+            union F { uint64_t d[2]; frag f; };
+            frag av[RTM][3];
+#pragma unroll
+            for (int i = 0; i < RTM; ++i)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    F f;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) f.d[h] = tr(pd[h] + 96 * i + 16 * q);
+                    av[i][q] = f.f;
+                }
+            constexpr int ta[6] = {0, 2, 1, 0, 1, 0}, tb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+            for (int j = 0; j < CTM; ++j) {
+                if (j < a.ctw) {
+                    frag bv[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        F f;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) f.d[h] = tr((one[j] ? a.cst : pi[h] + qoff[j]) + 16 * q);
+                        bv[q] = f.f;
+                    }
+                    f4 t[RTM];
+#pragma unroll
+                    for (int q = 0; q < 6; ++q)
+#pragma unroll
+                        for (int i = 0; i < RTM; ++i)
+                            t[i] = mfma_bf(av[i][ta[q]], bv[tb[q]], q ? t[i] : f4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                    for (int i = 0; i < RTM; ++i) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaf(t[i][r], sign, acc[i][j][r]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RTM; ++i)
+#pragma unroll
+        for (int j = 0; j < CTM; ++j) {
+            if (i >= rtn || j >= a.ctw) continue;
+            if (!a.each) {
+                *(f4 *)slot(i, j) = acc[i][j];
+            } else {
+                float *g = a.each + blockIdx.x * a.each_stride;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int o = 16 * (rt0 + i) + 4 * lg + r;
+                    const int dst = wgrad_index(ix, o, cqg, 4 * (tile0 + j) + (i16 >> 2), i16 & 3);
+                    if (dst >= 0) g[dst] = acc[i][j][r];
+                }
+            }
+        }
+}
+
+// Partial rows of every layer summed in order (compensated), into the
+// canonical gradient.
+struct ReduceDesc {
+    int first;           // first work item (one lane's four floats)
+    int rows, tiles_y, tgs, RTT;
+    int64_t base, rowsize;
+    FastDiv fRTT, ftiles_y, ftgs;
+    WgradIndex ix;
+};
+struct ReduceArgs {
+    const float *part;
+    float *dst;
+    int n_desc, items;
+    ReduceDesc d[kMaxLayers];
+};
+
+// A workgroup sums 64 items: wavefront w the rows w, w + 16, ... in order (16
+// chains of loads in flight instead of one: 65 us -> about 8 for 512 rows),
+// then the sixteen sums in order.
+constexpr int kReduceWaves = 16;
+__global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce_kernel(ReduceArgs a) {
+    __shared__ f4 part[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t = blockIdx.x * 64 + lane;  // (the layers' items come in whole 64s)
+    int k = 0;
+    while (k + 1 < a.n_desc && t >= a.d[k + 1].first) ++k;
+    const ReduceDesc &d = a.d[k];
+    const int e = t - d.first, tile = e >> 6;  // (column tile, row tile)
+    const float *src = a.part + d.base + (int64_t)e * 4;
+    f4 s = {0.f, 0.f, 0.f, 0.f}, comp = s;
+    auto add = [&](f4 v) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float y = v[q] - comp[q], w = s[q] + y;
+            comp[q] = (w - s[q]) - y;
+            s[q] = w;
+        }
+    };
+#pragma unroll 8
+    for (int r = wave; r < d.rows; r += kReduceWaves) add(*(const f4 *)(src + r * d.rowsize));
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave) return;
+    comp = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 1; w < kReduceWaves; ++w) add(part[w][lane]);
+    const int ct = fdiv(tile, d.fRTT), rt = tile - ct * d.RTT;
+    const int by = fdiv(ct, d.ftiles_y), cqg = fdiv(by, d.ftgs);
+    const int tl = (by - cqg * d.tgs) * d.tiles_y + ct - by * d.tiles_y;  // tile within the block of maps
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int dst = wgrad_index(d.ix, 16 * rt + 4 * (lane >> 4) + q, cqg, 4 * tl + ((lane & 15) >> 2), lane & 3);
+        if (dst >= 0) a.dst[dst] = s[q];
+    }
+}
+
+// ---- host ---------------------------------------------------------------------
+constexpr int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// bytes a position of C8 chunks takes in LDS: 48 per chunk, and an odd number
+// of 16-byte groups so that 16 consecutive positions fall in distinct banks
+int staged_bytes(int c8) { return 48 * c8 + (c8 % 2 ? 0 : 16); }
+
+int pool_kind(const Stage &g) { return g.p <= 2 ? g.p : 0; }
+
+RowDiv row_div(const Stage &g) {
+    return RowDiv{g.P, g.Wo, g.Pp, g.Wp, fast_div(g.P), fast_div(g.Wo), fast_div(g.Pp), fast_div(g.Wp)};
+}
+
+bool first_fits(const Stage &g, int S, FirstArgs &a, int64_t &bytes) {
+    a.S = S;
+    a.KS = (int)cdiv(g.K * g.K, 4);
+    a.OP = (int)cdiv(g.O, 16) * 16;
+    int64_t off = cdiv((int64_t)S * g.H * g.W, 4) * 4;
+    a.w_lds = (int)off;
+    off += (int64_t)4 * a.KS * a.OP;
+    a.k_lds = (int)off;
+    off += 4 * a.KS;
+    a.z_off = (int)off;
+    off += (int64_t)S * (pool_kind(g) == 0 ? g.P * g.O : pool_kind(g) == 2 ? g.nout : 0);
+    bytes = off * 4;
+    return bytes <= kLds;
+}
+
+// layers whose K is split over the wavefronts: at least four steps for each
+bool split_k(const Stage &g) { return g.KS >= 24; }
+
+struct FwdCfg {
+    int mt, nt, S, ctb, alias;
+    int64_t bytes;
+    int tab, red, z;
+};
+
+bool fwd_fits(const Stage &g, FwdCfg &c) {
+    const int wk = split_k(g) ? 4 : 1;
+    const int64_t in = cdiv((int64_t)c.S * g.H * g.W * g.st, 16) * 16, tab = 16 * (int64_t)g.KS;
+    const int64_t red = wk == 4 ? (int64_t)2 * c.mt * c.nt * 1024 : 0;
+    const int64_t z = pool_kind(g) == 0 ? (int64_t)c.S * g.P * std::min(g.O, 16 * c.ctb) * 4 : 0;
+    const int64_t jobs = cdiv((int64_t)c.S * g.P, 16 * c.mt) * cdiv(c.ctb, c.nt);
+    c.alias = jobs <= (wk == 4 ? 1 : 4);
+    c.tab = (int)in;
+    if (c.alias) {
+        c.red = 0;
+        c.z = (int)red;
+        c.bytes = std::max(in + tab, red + z);
+    } else {
+        c.red = (int)(in + tab);
+        c.z = (int)(in + tab + red);
+        c.bytes = in + tab + red + z;
+    }
+    return c.bytes <= kLds && in + tab <= kLds;
+}
+
+// tilings of each kind, largest first
+constexpr int kTile1[][2] = {{8, 4}, {8, 3}, {8, 1}, {2, 2}};
+constexpr int kTile4[][2] = {{5, 7}, {3, 7}, {2, 5}, {4, 1}};
+
+// Picks the samples per workgroup, the tiling and the column tiles per
+// workgroup: the least estimated time, from the matrix instructions of the
+// busiest wavefront, the staging and epilogue of a workgroup and the rounds
+// of workgroups over the compute units.
+bool pick_fwd(const Stage &g, int64_t n, FwdCfg &best) {
+    const bool k4 = split_k(g);
+    double least = 0;
+    bool found = false;
+    for (int t = 0; t < 4; ++t) {
+        FwdCfg c{};
+        c.mt = k4 ? kTile4[t][0] : kTile1[t][0];
+        c.nt = k4 ? kTile4[t][1] : kTile1[t][1];
+        for (int cgs = 1; cgs <= g.CT; cgs *= 2) {
+            c.ctb = (int)cdiv(g.CT, cgs);
+            const int64_t smax = std::min<int64_t>(n, 64);
+            for (c.S = 1; c.S <= smax; ++c.S) {
+                if (!fwd_fits(g, c)) break;
+                const double rg = (double)cdiv((int64_t)c.S * g.P, 16 * c.mt), cg = (double)cdiv(c.ctb, c.nt);
+                const double job = (k4 ? cdiv(g.KS, 4) : g.KS) * (c.mt * c.nt * 96.0 + 60.0) +
+                                   (k4 ? 40.0 * c.mt * c.nt + 400 : 0);
+                const double mm = job * (k4 ? rg * cg : (double)cdiv((int64_t)(rg * cg), 4));
+                const double stage = 1500 + (double)c.S * g.H * g.W * g.C8 * 0.9;
+                const double epi = 600 + (double)c.S * g.P * std::min(g.O, 16 * c.ctb) * 0.12 +
+                                   (double)c.S * g.Pp * std::min(g.O, 16 * c.ctb) * 0.5;
+                const int64_t blocks = cdiv(n, c.S) * cdiv(g.CT, c.ctb);
+                const int per_cu = (int)std::max<int64_t>(1, std::min<int64_t>(2, kLds / std::max<int64_t>(c.bytes, 1)));
+                // two workgroups on a CU share its matrix cores; staging and epilogue overlap
+                const double rounds = (double)cdiv(blocks, (int64_t)kCus * per_cu);
+                const double cost = rounds * (per_cu == 2 ? std::max(2 * mm, mm + stage + epi) : mm + stage + epi);
+                if (!found || cost < least) {
+                    least = cost;
+                    best = c;
+                    found = true;
+                }
+            }
+        }
+    }
+    return found;
+}
+
+template <int M, int N, int K>
+void launch_fwd(const FwdArgs &a, const FwdCfg &c, int pool, dim3 grid, hipStream_t s) {
+    if (pool == 1) conv_fwd_kernel<M, N, K, 1><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    else if (pool == 2) conv_fwd_kernel<M, N, K, 2><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    else conv_fwd_kernel<M, N, K, 0><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+}
+
+hipError_t run_fwd(const FwdArgs &a, const FwdCfg &c, bool k4, int pool, dim3 grid, hipStream_t s) {
+#define CHAOS_FWD(M, N, K)                                    if (c.mt == M && c.nt == N && k4 == (K == 4)) {               launch_fwd<M, N, K>(a, c, pool, grid, s);                 return hipGetLastError();                             }
+    CHAOS_FWD(8, 4, 1) CHAOS_FWD(8, 3, 1) CHAOS_FWD(8, 1, 1) CHAOS_FWD(2, 2, 1)
+    CHAOS_FWD(5, 7, 4) CHAOS_FWD(3, 7, 4) CHAOS_FWD(2, 5, 4) CHAOS_FWD(4, 1, 4)
+#undef CHAOS_FWD
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_pack(const BatchPlan &plan, const BatchWork &w, const BatchCall &c, bool grads, hipStream_t s) {
+    PackArgs a{};
+    a.params = c.params;
+    a.pack = w.pack;
+    for (int l = 1; l < plan.n_stages; ++l)
+        for (int back = 0; back < (grads ? 2 : 1); ++back) {
+            const Stage &g = plan.s[l];
+            PackDesc &d = a.d[a.n_desc++];
+            d.first = a.items;
+            d.back = back;
+            d.w_off = g.w_off;
+            d.w_stride = g.w_stride;
+            d.C = g.C;
+            d.C8 = g.C8;
+            d.T = g.T;
+            d.O = g.O;
+            d.KS = back ? g.KSO : g.KS;
+            d.CQ = (int)cdiv(g.C, 4);
+            d.flat = g.flat;
+            d.prevP = g.prevP;
+            d.fKS = fast_div(d.KS);
+            d.fC8 = fast_div(g.C8);
+            d.fC = fast_div(g.prevC);
+            d.fCQ = fast_div(d.CQ);
+            d.dst = back ? g.bpack : g.fpack;
+            a.items += (back ? g.RTB : g.CT) * d.KS * 64;
+        }
+    if (!a.items) return hipSuccess;
+    pack_kernel<<<(unsigned)cdiv(a.items, NT_), NT_, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+// ---- backward, host ----
+DeltaArgs delta_args(const Stage &g, const float *e, const float *y, const uint8_t *arg) {
+    return DeltaArgs{e, y, arg, g.O, g.O % 4 == 0, g.p, g.Wo, g.Wp, g.Pp, fast_div(g.p)};
+}
+
+// Backward data of a convolution: short K (up to 64 output maps) with the
+// deltas in registers, two workgroups to a CU; longer K with them in LDS.
+struct BackCfg {
+    int S, qb, qp, ES, d_off, sink;
+    bool longk;
+    int64_t bytes;
+};
+bool pick_back(const Stage &g, int64_t n, BackCfg &c) {
+    const int CQ = (int)cdiv(g.C, 4);
+    c.longk = g.KSO > 2;
+    const int nt = c.longk ? 9 : 4, nwv = c.longk ? 8 : 4;
+    bool found = false;
+    double least = 0;
+    for (int parts = 1; parts <= CQ; ++parts) {  // blocks of input maps
+        BackCfg t = c;
+        t.qb = (int)cdiv(CQ, parts);
+        if (parts > 1 && t.qb == (int)cdiv(CQ, parts - 1)) continue;
+        t.qp = c.longk ? (int)cdiv(t.qb, nwv) * nwv : std::max(t.qb, 4);
+        t.ES = 4 * (t.qb | 1);
+        for (t.S = 1; t.S <= 32 && t.S <= n; ++t.S) {
+            const int64_t err = (int64_t)t.S * g.H * g.W * t.ES * 4, d = (int64_t)16 * nt * g.ost;
+            t.d_off = (int)err;
+            t.sink = (int)(err + d);
+            t.bytes = err + d + 256;
+            if (t.bytes > kLds) break;
+            const int mt = c.longk ? 3 : 1;
+            const double jobs = (double)cdiv(cdiv(g.T, 4), mt) * t.qp, chunks = (double)cdiv((int64_t)t.S * g.P, 16 * nt);
+            const double wg = chunks * (cdiv((int64_t)jobs, nwv) * (g.KSO * 96.0 * mt * nt + 40.0 * mt * nt + 300) + 3000 +
+                                        16.0 * nt * g.O8 * 1.2) +
+                              2000 + err * 0.03;
+            const double per_cu = t.bytes <= kLds / 2 && !c.longk ? 2 : 1;
+            const double simd = c.longk ? 2 : 1;  // wavefronts of a workgroup on one matrix core
+            const double blocks = (double)cdiv(n, t.S) * cdiv(CQ, t.qb);
+            const double cost = std::ceil(blocks / (kCus * per_cu)) * wg * simd * (per_cu == 2 ? 1.5 : 1.0);
+            if (!found || cost < least) {
+                least = cost;
+                BackCfg k = t;
+                c = k;
+                found = true;
+            }
+        }
+    }
+    return found;
+}
+
+// Weight gradient of a layer.
+struct WgradCfg {
+    int rtm, ctm, wr;
+    int S, NB, RB, NCQ, C8s, sts, o8s, osts, tgs, ctw, kw, ncg, gz, tab, in_off, d_off, cst, npmax;
+    int im2col, C, T, CQ, RTT;
+    int64_t bytes, units, upc, chunks, rowsize;
+};
+bool wgrad_lds(const Stage &g, WgradCfg &c) {
+    const int64_t np = (int64_t)c.S * c.RB * g.Wo, npad = cdiv(np, 32) * 32;
+    const int64_t in = c.im2col ? np * c.sts : (int64_t)c.S * (c.RB + g.K - 1) * g.W * c.sts;
+    const int64_t slack = 96 * c.wr * c.rtm;
+    c.npmax = (int)npad;
+    c.tab = 0;
+    c.in_off = (int)(npad * 4);
+    c.d_off = (int)(c.in_off + cdiv(in, 16) * 16);
+    c.cst = (int)(c.d_off + np * c.osts + slack);
+    c.bytes = c.cst + 48 + c.osts + 96 + slack;
+    return c.bytes <= kLds;
+}
+bool pick_wgrad(const Stage &g, bool first, int64_t n, bool each, WgradCfg &c) {
+    c = WgradCfg{};
+    c.im2col = first;
+    c.C = first ? g.K * g.K : g.C;
+    c.T = first ? 1 : g.T;
+    c.CQ = (int)cdiv(c.C, 4);
+    c.RTT = (int)cdiv(g.O, 16);
+    c.rtm = c.RTT <= 1 ? 1 : c.RTT <= 2 ? 2 : c.RTT <= 8 ? 4 : 5;
+    c.wr = c.RTT <= 4 ? 1 : 2;
+    c.ctm = c.rtm == 5 ? 6 : 8;
+    c.gz = (int)cdiv(c.RTT, c.rtm * c.wr);
+    const int cap = 16 * c.ctm;  // quads of columns a workgroup holds
+    int ncq = std::max(1, (cap - 1) / c.T);
+    c.ncg = (int)cdiv(c.CQ, std::min(ncq, c.CQ));
+    c.NCQ = (int)cdiv(c.CQ, c.ncg);
+    const int tiles = (int)cdiv((int64_t)c.T * c.NCQ + 1, 4);
+    c.kw = each ? 1 : tiles == 1 ? 4 : tiles == 2 ? 2 : 1;
+    c.tgs = (int)cdiv(tiles, 4 * c.ctm);
+    c.ctw = (int)cdiv(cdiv(tiles, c.tgs), 4 / c.kw);
+    c.C8s = (int)cdiv(c.NCQ, 2);
+    c.sts = staged_bytes(c.C8s);
+    c.o8s = std::min(g.O8, 2 * c.rtm * c.wr);
+    c.osts = staged_bytes(c.o8s);
+    const int64_t budget = c.wr == 1 ? kLds / 2 : kLds;
+    const int64_t blocks_yz = (int64_t)c.ncg * c.tgs * c.gz, target = kCus * (c.wr == 1 ? 2 : 1);
+    c.RB = g.Ho;
+    c.NB = 1;
+    c.S = 1;
+    bool fits = wgrad_lds(g, c) && c.bytes <= budget;
+    if (fits && !each) {
+        // several samples to a unit: fewer padded K steps, fewer barriers
+        double best = 0;
+        int bs = 1;
+        for (c.S = 1; c.S <= 64; ++c.S) {
+            if (!wgrad_lds(g, c) || c.bytes > budget || (c.S > 1 && cdiv(n, c.S) * blocks_yz < target)) break;
+            const double eff = (double)c.S * g.P / ((double)cdiv((int64_t)c.S * g.P, 32) * 32 + 16);
+            if (eff > best * 1.01) {
+                best = eff;
+                bs = c.S;
+            }
+        }
+        c.S = bs;
+        wgrad_lds(g, c);
+    } else if (!fits) {
+        // bands of output rows, whole pooling windows
+        double best = 0;
+        int rb = 0;
+        for (int64_t bud = budget; !rb && bud <= kLds; bud += kLds / 2) {
+            for (c.RB = g.p; c.RB <= g.Ho; c.RB += g.p) {
+                if (!wgrad_lds(g, c) || c.bytes > bud) break;
+                double steps = 0;
+                for (int y = 0; y < g.Ho; y += c.RB) steps += 1.0 + cdiv((int64_t)std::min(c.RB, g.Ho - y) * g.Wo, 32);
+                if (1.0 / steps > best) {
+                    best = 1.0 / steps;
+                    rb = c.RB;
+                }
+            }
+        }
+        if (!rb) return false;
+        c.RB = rb;
+        c.NB = (int)cdiv(g.Ho, rb);
+        wgrad_lds(g, c);
+    }
+    c.units = cdiv(n, c.S) * c.NB;
+    if (each) {
+        c.upc = c.NB;
+        c.chunks = n;
+    } else {
+        c.chunks = std::max<int64_t>(1, std::min(c.units, cdiv(target, blocks_yz)));
+        c.upc = cdiv(c.units, c.chunks);
+        c.chunks = cdiv(c.units, c.upc);
+    }
+    c.rowsize = blocks_yz / c.gz * (4 / c.kw) * c.ctw * c.RTT * 256;
+    return true;
+}
+
+// sizes of the partial rows of every layer for n samples a pass
+struct PartPlan {
+    WgradCfg c[kMaxLayers];
+    int64_t base[kMaxLayers], total;
+};
+bool part_plan(const BatchPlan &plan, int64_t n, int64_t limit, PartPlan &p) {
+    int64_t row = 0;
+    p.total = 0;
+    for (int l = 0; l < plan.n_stages; ++l) {
+        if (!pick_wgrad(plan.s[l], l == 0, n, false, p.c[l])) return false;
+        p.total += p.c[l].chunks * p.c[l].kw * p.c[l].rowsize;
+        row += p.c[l].kw * p.c[l].rowsize;
+    }
+    if (p.total > limit) {
+        const int64_t most = limit / row;
+        if (most < 1) return false;
+        p.total = 0;
+        for (int l = 0; l < plan.n_stages; ++l) {
+            WgradCfg &c = p.c[l];
+            if (c.chunks > most) {
+                c.upc = cdiv(c.units, most);
+                c.chunks = cdiv(c.units, c.upc);
+            }
+            p.total += c.chunks * c.kw * c.rowsize;
+        }
+    }
+    int64_t off = 0;
+    for (int l = 0; l < plan.n_stages; ++l) {
+        p.base[l] = off;
+        off += p.c[l].chunks * p.c[l].kw * p.c[l].rowsize;
+    }
+    return true;
+}
+
+WgradIndex wgrad_index_of(const Stage &g, const WgradCfg &c) {
+    WgradIndex x{};
+    x.C = c.C;
+    x.T = c.T;
+    x.NCQ = c.NCQ;
+    x.CQ = c.CQ;
+    x.O = g.O;
+    x.cw_off = g.cw_off;
+    x.cb_off = g.cb_off;
+    x.rowlen = g.C * g.T;
+    x.flat = g.flat;
+    x.prevP = g.prevP;
+    x.wT = c.T;
+    x.fNCQ = fast_div(c.NCQ);
+    x.fprev = fast_div(g.prevC);
+    return x;
+}
+
+template <int RTM, int CTM, int WR>
+hipError_t run_wgrad(const WgradArgs &a, const WgradIndex &x, dim3 grid, int64_t bytes, hipStream_t s) {
+    conv_wgrad_kernel<RTM, CTM, WR><<<grid, 256 * WR, (size_t)bytes, s>>>(a, x);
+    return hipGetLastError();
+}
+
+hipError_t launch_wgrad(const Stage &g, const WgradCfg &c, const float *in, const float *e, const float *y,
+                        const uint8_t *arg, int64_t n, float *part, bool accumulate, float *each, int64_t each_stride,
+                        hipStream_t s) {
+    WgradArgs a{};
+    a.d = delta_args(g, e, y, arg);
+    a.in = in;
+    a.part = part;
+    a.n = n;
+    a.units = cdiv(n, c.S) * c.NB;
+    a.upc = c.upc;
+    a.S = c.S;
+    a.NB = c.NB;
+    a.RB = c.RB;
+    a.im2col = c.im2col;
+    a.vec_in = g.C % 4 == 0;
+    a.C = c.C;
+    a.W = g.W;
+    a.K = g.K;
+    a.T = c.T;
+    a.inrows = c.RB + g.K - 1;
+    a.Ho = g.Ho;
+    a.O = g.O;
+    a.NCQ = c.NCQ;
+    a.C8s = c.C8s;
+    a.sts = c.sts;
+    a.o8s = c.o8s;
+    a.osts = c.osts;
+    a.tgs = c.tgs;
+    a.ctw = c.ctw;
+    a.kw = c.kw;
+    a.CQ = c.CQ;
+    a.RTT = c.RTT;
+    a.tab = c.tab;
+    a.in_off = c.in_off;
+    a.d_off = c.d_off;
+    a.cst = c.cst;
+    a.accumulate = accumulate;
+    a.npmax = c.npmax;
+    a.rowsize = c.rowsize;
+    a.r = RowDiv{c.RB * g.Wo, g.Wo, g.Pp, g.Wp, fast_div(c.RB * g.Wo), fast_div(g.Wo), fast_div(g.Pp), fast_div(g.Wp)};
+    a.fC8s = fast_div(c.C8s);
+    a.fo8s = fast_div(c.o8s);
+    a.fNCQ = fast_div(c.NCQ);
+    a.fW = fast_div(g.W);
+    a.fK = fast_div(g.K);
+    a.ftgs = fast_div(c.tgs);
+    a.fHWs = fast_div(a.inrows * g.W);
+    a.each = each;
+    a.each_stride = each_stride;
+    const WgradIndex x = wgrad_index_of(g, c);
+    const dim3 grid((unsigned)cdiv(a.units, c.upc), (unsigned)(c.ncg * c.tgs), (unsigned)c.gz);
+    if (c.rtm == 1) return run_wgrad<1, 8, 1>(a, x, grid, c.bytes, s);
+    if (c.rtm == 2) return run_wgrad<2, 8, 1>(a, x, grid, c.bytes, s);
+    if (c.rtm == 4 && c.wr == 1) return run_wgrad<4, 8, 1>(a, x, grid, c.bytes, s);
+    if (c.rtm == 4) return run_wgrad<4, 8, 2>(a, x, grid, c.bytes, s);
+    return run_wgrad<5, 6, 2>(a, x, grid, c.bytes, s);
+}
+
+hipError_t launch_back(const Stage &g, const float *e, const float *y, const uint8_t *arg, const uint16_t *pack,
+                       float *out, int64_t n, hipStream_t s) {
+    if (g.flat) {
+        FlatArgs a{};
+        a.d = delta_args(g, e, y, arg);
+        a.pack = pack;
+        a.out = out;
+        a.n = n;
+        a.C = g.C;
+        a.RT = g.RTB;
+        a.KS = g.KSO;
+        a.O8 = g.O8;
+        a.ost = g.ost;
+        a.vec_out = g.C % 4 == 0;
+        a.fO8 = fast_div(g.O8);
+        const int64_t gx = cdiv(n, 64), most = cdiv(g.RTB, 16);
+        const unsigned gy = (unsigned)std::max<int64_t>(1, std::min(most, cdiv(kCus, gx)));
+        flat_back_kernel<<<dim3((unsigned)gx, gy), 512, (size_t)(64 * g.ost), s>>>(a);
+        return hipGetLastError();
+    }
+    BackCfg c{};
+    if (!pick_back(g, n, c)) return hipErrorInvalidValue;
+    BackArgs a{};
+    a.d = delta_args(g, e, y, arg);
+    a.pack = pack;
+    a.out = out;
+    a.n = n;
+    a.S = c.S;
+    a.HW = g.H * g.W;
+    a.W = g.W;
+    a.C = g.C;
+    a.CQ = (int)cdiv(g.C, 4);
+    a.T = g.T;
+    a.TG = (int)cdiv(g.T, 4);
+    a.K = g.K;
+    a.KS = g.KSO;
+    a.O8 = g.O8;
+    a.ost = g.ost;
+    a.qb = c.qb;
+    a.qp = c.qp;
+    a.ES = c.ES;
+    a.d_off = c.d_off;
+    a.sink = c.sink;
+    a.r = row_div(g);
+    a.fO8 = fast_div(g.O8);
+    a.fqp = fast_div(c.qp);
+    a.fK = fast_div(g.K);
+    a.fES = fast_div(c.ES);
+    const dim3 grid((unsigned)cdiv(n, c.S), (unsigned)cdiv(a.CQ, c.qb));
+    if (c.longk) conv_back_kernel<3, 9, 8, 0><<<grid, 512, (size_t)c.bytes, s>>>(a);
+    else if (g.KSO == 1) conv_back_kernel<1, 4, 4, 1><<<grid, 256, (size_t)c.bytes, s>>>(a);
+    else conv_back_kernel<1, 4, 4, 2><<<grid, 256, (size_t)c.bytes, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_forward(const BatchPlan &plan, const BatchWork &w, const BatchCall &c, int64_t i0, int64_t n,
+                          bool args, hipStream_t s) {
+    for (int l = 0; l < plan.n_stages; ++l) {
+        const Stage &g = plan.s[l];
+        float *y = w.act + w.samples * g.y_off;
+        uint8_t *arg = (args && g.p > 1) ? w.arg + w.samples * g.a_off : nullptr;
+        if (l == 0) {
+            FirstArgs a{};
+            int64_t bytes = 0;
+            // several samples to a workgroup (one copy of the weights) once
+            // every CU has eight workgroups, four of which fit its LDS
+            int S = 1;
+            while (S < 4 && cdiv(n, S + 1) >= 8 * kCus && first_fits(g, S + 1, a, bytes) && bytes <= kLds / 4) ++S;
+            first_fits(g, S, a, bytes);
+            a.x = c.x + i0 * g.H * g.W;
+            a.params = c.params;
+            a.y = y;
+            a.arg = arg;
+            a.n = n;
+            a.HW = g.H * g.W;
+            a.W = g.W;
+            a.K = g.K;
+            a.KK = g.K * g.K;
+            a.O = g.O;
+            a.p = g.p;
+            a.nout = g.nout;
+            a.w_off = g.w_off;
+            a.w_stride = g.w_stride;
+            a.b_off = g.b_off;
+            a.d = row_div(g);
+            a.fK = fast_div(g.K);
+            a.fO = fast_div(g.O);
+            a.fOP = fast_div(a.OP);
+            const unsigned grid = (unsigned)cdiv(n, S);
+            const int pool = pool_kind(g);
+            if (a.OP <= 16) {
+                if (pool == 1) conv_first_kernel<1, 1><<<grid, NT_, (size_t)bytes, s>>>(a);
+                else if (pool == 2) conv_first_kernel<2, 1><<<grid, NT_, (size_t)bytes, s>>>(a);
+                else conv_first_kernel<0, 1><<<grid, NT_, (size_t)bytes, s>>>(a);
+            } else {
+                if (pool == 1) conv_first_kernel<1, 2><<<grid, NT_, (size_t)bytes, s>>>(a);
+                else if (pool == 2) conv_first_kernel<2, 2><<<grid, NT_, (size_t)bytes, s>>>(a);
+                else conv_first_kernel<0, 2><<<grid, NT_, (size_t)bytes, s>>>(a);
+            }
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        FwdCfg f{};
+        if (!pick_fwd(g, n, f)) return hipErrorInvalidValue;
+        FwdArgs a{};
+        a.in = w.act + w.samples * plan.s[l - 1].y_off;
+        a.bias = c.params + g.b_off;
+        a.pack = w.pack + g.fpack;
+        a.y = y;
+        a.arg = arg;
+        a.n = n;
+        a.S = f.S;
+        a.HW = g.H * g.W;
+        a.W = g.W;
+        a.C = g.C;
+        a.C8 = g.C8;
+        a.st = g.st;
+        a.K = g.K;
+        a.T = g.T;
+        a.vec = g.C % 4 == 0;
+        a.O = g.O;
+        a.p = g.p;
+        a.nout = g.nout;
+        a.KS = g.KS;
+        a.CT = g.CT;
+        a.ctb = f.ctb;
+        a.tab = f.tab;
+        a.red = f.red;
+        a.z = f.z;
+        a.alias = f.alias;
+        a.fC8 = fast_div(g.C8);
+        a.d = row_div(g);
+        a.fK = fast_div(g.K);
+        const int gy = (int)cdiv(g.CT, f.ctb);
+        a.fon = fast_div(std::min(g.O, 16 * f.ctb));
+        a.fon_last = fast_div(g.O - 16 * f.ctb * (gy - 1));
+        hipError_t e = run_fwd(a, f, split_k(g), pool_kind(g), dim3((unsigned)cdiv(n, f.S), (unsigned)gy), s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+} // namespace
+
+void batch_plan(const Net &net, const ParamLayout &layout, BatchPlan &plan) {
+    plan = BatchPlan{};
+    if (net.n_layers < 1 || net.L[0].kind != kConv) return;
+    auto dev = [&](int64_t i) -> int64_t {
+        for (int k = 0; k < layout.n_seg; ++k) {
+            const ParamSegment &q = layout.seg[k];
+            const int64_t r0 = i - q.can_off;
+            if (r0 >= 0 && r0 < (int64_t)q.rows * q.len) return q.dev_off + r0 / q.len * q.dev_stride + r0 % q.len;
+        }
+        return -1;
+    };
+    int64_t act = 0, arg = 0, pack = 0, rows = 0;
+    int n = 0;
+    for (int l = 0; l < net.n_layers; ++l) {
+        const Layer &ly = net.L[l];
+        if (ly.kind == kPool) return;  // a pooling layer not right after a convolution or FC layer
+        Stage &g = plan.s[n];
+        g = Stage{};
+        g.flat = ly.kind == kFc;
+        g.O = ly.cout;
+        if (g.flat) {
+            g.C = ly.nin;
+            g.H = g.W = g.K = g.Ho = g.Wo = 1;
+            g.prevC = n ? plan.s[n - 1].O : 1;
+            g.prevP = n ? plan.s[n - 1].Pp : ly.nin;
+        } else {
+            g.C = ly.cin;
+            g.H = ly.hin;
+            g.W = ly.win;
+            g.K = ly.k;
+            g.Ho = ly.hout;
+            g.Wo = ly.wout;
+            g.prevC = 1;
+            g.prevP = 1;
+        }
+        g.p = 1;
+        g.Hp = g.Ho;
+        g.Wp = g.Wo;
+        if (l + 1 < net.n_layers && net.L[l + 1].kind == kPool) {
+            ++l;
+            g.p = net.L[l].k;
+            g.Hp = net.L[l].hout;
+            g.Wp = net.L[l].wout;
+            if (g.p > 16) return;  // the window element is kept in a byte
+        }
+        g.P = g.Ho * g.Wo;
+        g.Pp = g.Hp * g.Wp;
+        g.T = g.K * g.K;
+        g.nin = g.C * g.H * g.W;
+        g.nout = g.O * g.Pp;
+        g.cw_off = ly.w_off;
+        g.cb_off = ly.b_off;
+        g.w_off = (int)dev(ly.w_off);
+        g.w_stride = ly.cout > 1 ? (int)(dev(ly.w_off + ly.nw / ly.cout) - dev(ly.w_off)) : 0;
+        g.b_off = (int)dev(ly.b_off);
+        g.C8 = (int)cdiv(g.C, 8);
+        g.st = staged_bytes(g.C8);
+        g.O8 = (int)cdiv(g.O, 8);
+        g.ost = staged_bytes(g.O8);
+        g.CT = (int)cdiv(g.O, 16);
+        g.KS = (int)cdiv((int64_t)g.T * g.C8, 4);
+        g.KSO = (int)cdiv(g.O8, 4);
+        // index arithmetic by FastDiv: products of an index and a divisor stay in 32 bits
+        if ((int64_t)g.nin > 65536 || (int64_t)g.O * g.P > 262144 || (int64_t)g.CT * g.KS * g.KS > (1 << 30) ||
+            (int64_t)g.KS * 4 > 65536)
+            return;
+        g.y_off = act;
+        act += g.nout;
+        if (g.p > 1) {
+            g.a_off = arg;
+            arg += g.nout;
+        }
+        if (n == 0) {
+            FirstArgs a{};
+            int64_t bytes = 0;
+            if (!first_fits(g, 1, a, bytes)) return;
+        } else {
+            g.RTB = g.flat ? (int)cdiv(g.C, 16) : (int)(cdiv(g.T, 4) * cdiv(g.C, 4));
+            g.fpack = pack;
+            pack += (int64_t)g.CT * g.KS * 3 * 512;
+            g.bpack = pack;
+            pack += (int64_t)g.RTB * g.KSO * 3 * 512;
+            FwdCfg c{};
+            BackCfg bc{};
+            if (!pick_fwd(g, 1, c) || (!g.flat && !pick_back(g, 1, bc)) || 64 * (int64_t)g.ost > kLds) return;
+            if ((int64_t)g.RTB * g.KSO * g.KSO > (1 << 26)) return;
+        }
+        WgradCfg wc{};
+        if (!pick_wgrad(g, n == 0, 1, false, wc) || wc.rowsize / 256 * wc.RTT > (1 << 30)) return;
+        rows += wc.rowsize;
+        ++n;
+    }
+    if (rows > (1 << 28) || pack > (int64_t)1 << 30) return;
+    plan.n_stages = n;
+    plan.pack_elems = pack;
+    plan.act_floats = cdiv(act, 4) * 4;
+    plan.arg_bytes = cdiv(arg, 16) * 16;
+    plan.last_c = plan.s[n - 1].O;
+    plan.last_p = plan.s[n - 1].Pp;
+    plan.ok = true;
+}
+
+int64_t batch_sample_bytes(const BatchPlan &plan, bool grads) {
+    return plan.act_floats * 4 * (grads ? 2 : 1) + (grads ? plan.arg_bytes : 0);
+}
+
+int64_t batch_part_floats(const BatchPlan &plan, int64_t n) {
+    PartPlan p;
+    return part_plan(plan, n, (int64_t)1 << 60, p) ? p.total : 0;
+}
+
+int64_t batch_part_min(const BatchPlan &plan) {
+    PartPlan p;
+    if (!part_plan(plan, 1, (int64_t)1 << 60, p)) return (int64_t)1 << 60;
+    int64_t row = 0;
+    for (int l = 0; l < plan.n_stages; ++l) row += 4 * p.c[l].rowsize;
+    return row;
+}
+
+hipError_t launch_batch(const BatchPlan &plan, const BatchWork &w, const BatchCall &c, hipStream_t s) {
+    const bool grads = c.grad_sum || c.grad_each;
+    hipError_t e = launch_pack(plan, w, c, grads, s);
+    if (e != hipSuccess) return e;
+    PartPlan parts;
+    if (c.grad_sum && !part_plan(plan, std::min(w.samples, c.n), w.part_floats, parts)) return hipErrorInvalidValue;
+    const int last = plan.n_stages - 1;
+    float *err = w.act + w.samples * plan.act_floats;  // errors, laid out as the activations
+    for (int64_t i0 = 0; i0 < c.n; i0 += w.samples) {
+        const int64_t n = std::min(w.samples, c.n - i0);
+        if ((e = launch_forward(plan, w, c, i0, n, grads, s)) != hipSuccess) return e;
+        LossArgs a{};
+        a.y = w.act + w.samples * plan.s[last].y_off;
+        a.labels = c.labels + i0;
+        a.n = n;
+        a.C = plan.last_c;
+        a.P = plan.last_p;
+        a.out = c.out ? c.out + i0 * a.C * a.P : nullptr;
+        a.loss = c.loss ? c.loss + i0 : nullptr;
+        a.e = grads ? err + w.samples * plan.s[last].y_off : nullptr;
+        a.n_wrong = c.n_wrong;
+        loss_kernel<<<(unsigned)cdiv(n, NT_), NT_, 0, s>>>(a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (!grads) continue;
+        for (int l = last; l >= 0; --l) {
+            const Stage &g = plan.s[l];
+            const float *y = w.act + w.samples * g.y_off, *el = err + w.samples * g.y_off;
+            const uint8_t *arg = g.p > 1 ? w.arg + w.samples * g.a_off : nullptr;
+            const float *in = l ? w.act + w.samples * plan.s[l - 1].y_off : c.x + i0 * g.H * g.W;
+            if (c.grad_sum &&
+                (e = launch_wgrad(g, parts.c[l], in, el, y, arg, n, w.part + parts.base[l], i0 > 0, nullptr, 0, s)) !=
+                    hipSuccess)
+                return e;
+            if (c.grad_each) {
+                WgradCfg each;
+                if (!pick_wgrad(g, l == 0, n, true, each)) return hipErrorInvalidValue;
+                if ((e = launch_wgrad(g, each, in, el, y, arg, n, nullptr, false, c.grad_each + i0 * c.n_params,
+                                      c.n_params, s)) != hipSuccess)
+                    return e;
+            }
+            if (l && (e = launch_back(g, el, y, arg, w.pack + g.bpack, err + w.samples * plan.s[l - 1].y_off, n, s)) !=
+                         hipSuccess)
+                return e;
+        }
+    }
+    if (c.grad_sum) {
+        ReduceArgs a{};
+        a.part = w.part;
+        a.dst = c.grad_sum;
+        for (int l = 0; l < plan.n_stages; ++l) {
+            const WgradCfg &k = parts.c[l];
+            ReduceDesc &d = a.d[a.n_desc++];
+            d.first = a.items;
+            d.rows = (int)(k.chunks * k.kw);
+            d.tiles_y = 4 / k.kw * k.ctw;
+            d.tgs = k.tgs;
+            d.RTT = k.RTT;
+            d.base = parts.base[l];
+            d.rowsize = k.rowsize;
+            d.fRTT = fast_div(k.RTT);
+            d.ftiles_y = fast_div(d.tiles_y);
+            d.ftgs = fast_div(k.tgs);
+            d.ix = wgrad_index_of(plan.s[l], k);
+            a.items += (int)(k.rowsize / 4);
+        }
+        wgrad_reduce_kernel<<<(unsigned)(a.items / 64), 64 * kReduceWaves, 0, s>>>(a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+} // namespace chaos

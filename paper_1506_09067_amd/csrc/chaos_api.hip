@@ -2,6 +2,7 @@
 // device memory owned by a net, and the launches behind every entry point
 // declared in include/chaos.h.
 #include "../../include/chaos.h"
+#include "batch.h"
 #include "chaos_internal.h"
 
 #include <algorithm>
@@ -40,16 +41,18 @@ struct chaos_net {
     float *sess_loss = nullptr;   // session: per-sample losses (training, then test)
     int64_t sess_loss_n = 0;
     int32_t *sess_wrong = nullptr;  // 64 bytes: [0] wrong count (int32), float [8] reference loss
-    float *stash = nullptr;       // large net, batch gradient: per-sample conv3 / FC1 operands
-    int64_t stash_n = 0;          // samples the stash holds
-    float *bpart = nullptr;       // their chunk partial sums: conv3 rows, then FC1 rows
-    int64_t bpart_chunks = 0;
     int push_delay = 1;           // samples between a worker's pushes (atomic Hogwild)
     int n_replicas = 1;           // weight replicas read by the workers (atomic Hogwild)
     int refresh_every = 1;        // samples per replica between its refreshes
     float *replicas = nullptr;    // [n_replicas][device floats]
     int32_t *rep_counter = nullptr;  // [n_replicas]
     int delay_max_workers = 0;    // resident workers of the delayed-push kernel (0 = none)
+    chaos::BatchPlan plan;        // how the batched engine serves this net (plan.ok: it does)
+    uint16_t *pack = nullptr;     // its weights in operand order
+    void *act = nullptr;          // its activations, allocated with the net
+    int64_t act_bytes = 0;
+    void *grad_act = nullptr;     // and those of a gradient, allocated on first use
+    int64_t grad_bytes = 0;
 };
 
 // Partial-sum rows of chaos_forward_backward_noalloc: a fixed array on every
@@ -229,6 +232,59 @@ int noalloc_scratch(int device, float **out) {
     return CHAOS_OK;
 }
 
+// Activation workspace of the batched engine.  That of a forward pass is
+// allocated with the net, so that no later one allocates; a gradient's grows on
+// use.  Each is bounded: more samples go through it in several passes.
+constexpr int64_t kActBytes = (int64_t)96 << 20, kGradBytes = (int64_t)768 << 20, kPassSamples = 16384;
+
+// samples (a multiple of 4) of a pass over n samples in a workspace of `bytes`
+int64_t pass_samples(const chaos_net *net, int64_t n, int64_t bytes, bool grads) {
+    const int64_t each = chaos::batch_sample_bytes(net->plan, grads);
+    int64_t fit = std::min(bytes / each, kPassSamples);
+    // whole rounds of one workgroup per compute unit
+    if (fit >= 256) fit = fit / 256 * 256;
+    return std::min((n + 3) / 4 * 4, fit / 4 * 4);
+}
+
+// Which calls go to the batched engine.  A net's own kernel runs a sample from
+// the image to its gradient in one workgroup, so up to one sample per compute
+// unit it takes one sample's time; the engine's launches (one per layer and
+// direction) take longer than that, but spread a few samples over the whole GPU
+// and keep the matrix cores busy with many.  Measured, us (own kernel / engine):
+//   evaluate  large 256: 84 / 110, 300: 163 / 125, 10000: 3166 / 1720;
+//             medium 300: 63 / 71, 10000: 1143 / 584; small 10000: 199 / 252
+//   gradient  medium 16: 158 / 172, 1024: 537 / 338; small 16: 43 / 139,
+//             16384: 1063 / 1597
+// (the large nets' own kernels have no frozen-weight gradient).  Per-sample
+// gradients always take the engine, so that a max-pool near-tie is resolved as
+// in the sums they are compared with.
+bool batched_evaluate(const chaos_net *net, int64_t n) {
+    if (!net->plan.ok) return false;
+    if (net->fused || net->t1) return n > net->cus;
+    if (net->cpcp) return net->cpcp == 2 && n >= 1024;
+    return true;
+}
+bool batched_gradient(const chaos_net *net, int64_t n, const float *sum, const float *each) {
+    if (!net->plan.ok || !(sum || each)) return false;
+    if (net->cpcp && !each) return net->cpcp == 2 && n >= 512;
+    return true;
+}
+
+hipError_t batch_gradient(chaos_net *net, const chaos::BatchWork &w, const float *x, const int32_t *labels, int64_t n,
+                          float *out, float *loss, float *grad_sum, float *grad_each, hipStream_t s) {
+    chaos::BatchCall c{};
+    c.params = net->params;
+    c.x = x;
+    c.labels = labels;
+    c.n = n;
+    c.out = out;
+    c.loss = loss;
+    c.grad_sum = grad_sum;
+    c.grad_each = grad_each;
+    c.n_params = net->n_params;
+    return chaos::launch_batch(net->plan, w, c, s);
+}
+
 hipError_t launch(chaos_net *net, int mode, const chaos::WorkArgs &a, int grid, hipStream_t s) {
     if (net->fused) return chaos::launch_fused_large(mode, a, grid, s);
     if (net->t1) return chaos::launch_fused_t1(mode, a, grid, s);
@@ -311,6 +367,16 @@ int chaos_create_net(int32_t in_h, int32_t in_w, const chaos_layer *layers, int3
     if (e == hipSuccess)
         e = hipMemcpy(net->params, init, (size_t)net->layout.n_dev * sizeof(float),
                       hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        if (chaos::batch_plan) chaos::batch_plan(desc, net->layout, net->plan);
+        // at least four samples of a gradient
+        if (net->plan.ok && 4 * chaos::batch_sample_bytes(net->plan, true) > kActBytes) net->plan.ok = false;
+        if (net->plan.ok) {
+            net->act_bytes = std::min(kActBytes, kPassSamples * chaos::batch_sample_bytes(net->plan, true));
+            e = hipMalloc(&net->pack, (size_t)std::max<int64_t>(net->plan.pack_elems, 8) * sizeof(uint16_t));
+            if (e == hipSuccess) e = hipMalloc(&net->act, (size_t)net->act_bytes);
+        }
+    }
     if (e != hipSuccess) {
         chaos_destroy_net(net);
         return e == hipErrorOutOfMemory ? fail(CHAOS_ENOMEM, "device allocation failed")
@@ -331,10 +397,11 @@ int chaos_destroy_net(chaos_net *net) {
     (void)hipFree(net->wide_scratch);
     (void)hipFree(net->sess_loss);
     (void)hipFree(net->sess_wrong);
-    (void)hipFree(net->stash);
-    (void)hipFree(net->bpart);
     (void)hipFree(net->replicas);
     (void)hipFree(net->rep_counter);
+    (void)hipFree(net->pack);
+    (void)hipFree(net->act);
+    (void)hipFree(net->grad_act);
     delete net;
     return ok();
 }
@@ -554,6 +621,27 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
             HIP_TRY(chaos::launch_fill_f32(grad_sum_dev, 0.0f, net->n_params, stream), "zero grad");
         return ok();
     }
+    if (batched_gradient(net, n, grad_sum_dev, grad_each_dev)) {
+        const int64_t samples = pass_samples(net, n, kGradBytes, true);
+        const int64_t part = grad_sum_dev ? chaos::batch_part_floats(net->plan, std::min(samples, n)) : 0;
+        const int64_t act = samples * chaos::batch_sample_bytes(net->plan, true), need = act + part * 4;
+        if (need > net->grad_bytes) {
+            (void)hipFree(net->grad_act);
+            net->grad_act = nullptr;
+            net->grad_bytes = 0;
+            if (hipMalloc(&net->grad_act, (size_t)need) != hipSuccess) {
+                net->grad_act = nullptr;
+                return fail(CHAOS_ENOMEM, "gradient workspace of %lld bytes", (long long)need);
+            }
+            net->grad_bytes = need;
+        }
+        chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->grad_act, samples, true);
+        w.part = reinterpret_cast<float *>(static_cast<char *>(net->grad_act) + act);
+        w.part_floats = part;
+        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
+                "forward_backward launch");
+        return ok();
+    }
     int grid = (int)std::min<int64_t>(net->max_workers, n);
     if (grad_sum_dev) {
         // fixed sample -> worker assignment (sample i goes to worker i mod grid,
@@ -569,40 +657,11 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
         }
         grid = want;
     }
-    // large net, gradient sum only: the conv3 and FC1 weight gradients are
-    // contracted over the batch on the matrix cores from per-sample operands
-    // the kernel leaves in HBM (47.6 KB per sample, allocated on first use)
-    const bool batched = grad_sum_dev && !grad_each_dev && net->fused;
-    constexpr int64_t kConv3W = 100 * 2160, kFc1W = 150 * 900;
-    if (batched) {
-        if (n > net->stash_n) {
-            (void)hipFree(net->stash);
-            net->stash = nullptr;
-            net->stash_n = 0;
-            if (hipMalloc(&net->stash, (size_t)n * chaos::kStashFloats * sizeof(float)) != hipSuccess) {
-                net->stash = nullptr;
-                return fail(CHAOS_ENOMEM, "batch gradient operands for %lld samples", (long long)n);
-            }
-            net->stash_n = n;
-        }
-        const int64_t nc = chaos::batch_grad_chunks(n);
-        if (nc > net->bpart_chunks) {
-            (void)hipFree(net->bpart);
-            net->bpart = nullptr;
-            net->bpart_chunks = 0;
-            if (hipMalloc(&net->bpart, (size_t)nc * (kConv3W + kFc1W) * sizeof(float)) != hipSuccess) {
-                net->bpart = nullptr;
-                return fail(CHAOS_ENOMEM, "batch gradient partial sums");
-            }
-            net->bpart_chunks = nc;
-        }
-    }
     chaos::WorkArgs a = base_args(net, x_dev, labels_dev, n);
     a.out = out_dev;
     a.loss = loss_dev;
     a.grad_each = grad_each_dev;
     a.grad_part = grad_sum_dev ? net->grad_part : nullptr;
-    a.stash = batched ? net->stash : nullptr;
     if (grad_sum_dev)
         HIP_TRY(chaos::launch_fill_f32(net->grad_part, 0.0f, (int64_t)grid * net->n_params, stream),
                 "zero partial sums");
@@ -611,19 +670,6 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
         HIP_TRY(chaos::launch_reduce_partials(net->grad_part, grid, net->n_params, grad_sum_dev,
                                               stream),
                 "reduce");
-    if (batched) {
-        // the per-sample pass pushed nothing into these two weight blocks:
-        // their sums replace the zeros the reduction left there
-        const int64_t nc = chaos::batch_grad_chunks(n);
-        float *part3 = net->bpart, *partf = net->bpart + nc * kConv3W;
-        HIP_TRY(chaos::launch_batch_grad(net->stash, n, part3, partf, stream), "batch gradient");
-        HIP_TRY(chaos::launch_reduce_partials(part3, nc, kConv3W, grad_sum_dev + net->desc.L[3].w_off,
-                                              stream),
-                "reduce conv3");
-        HIP_TRY(chaos::launch_reduce_partials(partf, nc, kFc1W, grad_sum_dev + net->desc.L[5].w_off,
-                                              stream),
-                "reduce FC1");
-    }
     return ok();
 }
 
@@ -714,12 +760,22 @@ int chaos_forward_backward_noalloc(chaos_net *net, const float *x_dev, const int
             HIP_TRY(chaos::launch_fill_f32(grad_sum_dev, 0.0f, net->n_params, stream), "zero grad");
         return ok();
     }
+    if (batched_gradient(net, n, grad_sum_dev, grad_each_dev) &&
+        (!grad_sum_dev || chaos::batch_part_min(net->plan) <= kNoAllocFloats)) {
+        // as chaos_forward_backward, in the workspace allocated with the net and
+        // with as many partial-sum rows as the fixed scratch holds
+        chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
+                                               pass_samples(net, n, net->act_bytes, true), true);
+        w.part = rows;
+        w.part_floats = kNoAllocFloats;
+        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
+                "forward_backward launch");
+        return ok();
+    }
     // as chaos_forward_backward: sample i goes to worker i mod grid, each
     // worker adds its samples' gradients into its own row in sample order,
     // then the rows are summed in a fixed order; here the grid is bounded by
-    // the rows that fit in the fixed scratch (and the large net's conv3 / FC1
-    // gradients are pushed per sample instead of contracted over the batch,
-    // which would need per-sample operands in memory)
+    // the rows that fit in the fixed scratch
     int grid = (int)std::min<int64_t>(net->max_workers, n);
     if (grad_sum_dev) grid = (int)std::min<int64_t>({(int64_t)grid, 512, kNoAllocFloats / net->n_params});
     chaos::WorkArgs a = base_args(net, x_dev, labels_dev, n);
@@ -745,6 +801,19 @@ int chaos_evaluate(chaos_net *net, const float *x_dev, const int32_t *labels_dev
     if (int rc = set_device(net)) return rc;
     HIP_TRY(chaos::launch_fill_i32(n_wrong_dev, 0, 1, stream), "zero n_wrong");
     if (n == 0) return ok();
+    if (batched_evaluate(net, n)) {
+        chaos::BatchCall c{};
+        c.params = net->params;
+        c.x = x_dev;
+        c.labels = labels_dev;
+        c.n = n;
+        c.out = out_dev;
+        c.n_wrong = n_wrong_dev;
+        const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
+                                                     pass_samples(net, n, net->act_bytes, false), false);
+        HIP_TRY(chaos::launch_batch(net->plan, w, c, stream), "evaluate launch");
+        return ok();
+    }
     int grid = (int)std::min<int64_t>(net->max_workers, n);
     chaos::WorkArgs a = base_args(net, x_dev, labels_dev, n);
     a.out = out_dev;

@@ -493,8 +493,8 @@ __global__ void __launch_bounds__(NT, 1) fused_large_kernel(WorkArgs a) {
         push.mode = MODE;
         push.params = a.params;
         push.neg_lr = -a.lr;
-        push.each = a.grad_each ? a.grad_each + idx * (int64_t)NPARAM : nullptr;
-        push.part = a.grad_part ? a.grad_part + (int64_t)blockIdx.x * NPARAM : nullptr;
+        push.each = nullptr;
+        push.part = nullptr;
 
         // output layer: E = 1/2 sum (y - t)^2, delta = (y - t) f'(z)
         if (tid < 64) {
@@ -507,6 +507,12 @@ __global__ void __launch_bounds__(NT, 1) fused_large_kernel(WorkArgs a) {
             }
             e = wave_sum(e);
             if (tid == 0 && a.loss) a.loss[idx] = 0.5f * e;
+        }
+        if constexpr (MODE == kForwardBackward) {
+            // outputs and losses at frozen weights, the bits of a training pass at
+            // lr 0 (gradients are the batched engine's)
+            __syncthreads();
+            continue;
         }
         __syncthreads();
         // FC2 backward data (pre-update weights)
@@ -533,128 +539,70 @@ __global__ void __launch_bounds__(NT, 1) fused_large_kernel(WorkArgs a) {
         }
         if (tid < F2) push(DBF2 + tid, OBF2 + tid, sm.dout[tid]);
         if (tid < F1) push(DBF1 + tid, OBF1 + tid, sm.dh[tid]);
-        if constexpr (MODE == kForwardBackward) {
-            // frozen weights: read them (16-byte loads, ten rows per batch,
-            // the next batch requested while this one is summed), then push
-            if (tid < NF1 / 4) {
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-                f4 wa[10], wb[10];
-                auto load = [&](f4 (&w)[10], int j0) {
+        {
+            float xv[15], ep[15];
 #pragma unroll
-                    for (int jj = 0; jj < 10; ++jj)
-                        w[jj] = *(const f4 *)(W + DF1 + (j0 + jj) * NF1S + 4 * tid);
-                };
-                auto comp = [&](const f4 (&w)[10], int j0) {
-#pragma unroll
-                    for (int jj = 0; jj < 10; ++jj) {
-                        float d = sm.dh[j0 + jj];
-                        acc.x = fmaf(w[jj].x, d, acc.x);
-                        acc.y = fmaf(w[jj].y, d, acc.y);
-                        acc.z = fmaf(w[jj].z, d, acc.z);
-                        acc.w = fmaf(w[jj].w, d, acc.w);
-                    }
-                };
-                load(wa, 0);
-                for (int j0 = 0; j0 < F1; j0 += 20) {
-                    if (j0 + 10 < F1) load(wb, j0 + 10);
-                    comp(wa, j0);
-                    if (j0 + 10 < F1) {
-                        if (j0 + 20 < F1) load(wa, j0 + 20);
-                        comp(wb, j0 + 10);
-                    }
-                }
-                *(f4 *)(sm.e3 + 4 * tid) = acc;
+            for (int c = 0; c < 15; ++c) {
+                int i = lane + 64 * c;
+                xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
+                ep[c] = 0.0f;
             }
-            if (a.stash) {
-                // batched gradient: this sample's FC1 deltas and inputs go to
-                // HBM; the FC1 weight gradient is contracted over the batch
-                // afterwards
-                float *dhs = a.stash + a.n * (int64_t)(C3 * M3 + C2 * NY2) + idx * F1;
-                float *p3s = a.stash + a.n * (int64_t)(C3 * M3 + C2 * NY2 + F1) + idx * NF1;
-                if (tid < F1) dhs[tid] = sm.dh[tid];
-                for (int i = tid; i < NF1; i += NT) p3s[i] = sm.p3[i];
-            } else {
-                float xv[15];
+            // The wavefront's rows j = wave + NW r (r < 38) in half-steps
+            // of FC1_ROWS / 2 rows: the next half-step's pushes are issued
+            // before the current one's returns are summed, so about
+            // 15 FC1_ROWS pushes stay in flight throughout (a row is summed
+            // once all its returns are in, rows in increasing order).
+            constexpr int HR = FC1_ROWS / 2, NR = (F1 + NW - 1) / NW;
+            static_assert(NR % (2 * HR) == HR, "38 rows: pairs of half-steps and a last half-step");
+            float oldA[HR][15], oldB[HR][15];
+            auto issue = [&](float (&o)[HR][15], int r0) {
 #pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
-                }
-                for (int j = wave; j < F1; j += NW) {
-                    const float d = sm.dh[j];
+                for (int r = 0; r < HR; ++r) {
+                    const int jr = wave + NW * (r0 + r);
+                    const float d = (jr < F1) ? sm.dh[jr] : 0.0f;
 #pragma unroll
                     for (int c = 0; c < 15; ++c) {
-                        int i = lane + 64 * c;
-                        if (i < NF1) push(DF1 + j * NF1S + i, OF1 + j * NF1 + i, d * xv[c]);
+                        const int i = lane + 64 * c;
+                        o[r][c] = (jr < F1 && i < NF1) ? push.with_old(DF1 + jr * NF1S + i, OF1 + jr * NF1 + i, d * xv[c])
+                                                       : 0.0f;
                     }
                 }
-            }
-        } else {
-            {
-                float xv[15], ep[15];
+            };
+            auto consume = [&](const float (&o)[HR][15], int r0) {
 #pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
-                    ep[c] = 0.0f;
+                for (int r = 0; r < HR; ++r) {
+                    const int jr = wave + NW * (r0 + r);
+                    const float d = (jr < F1) ? sm.dh[jr] : 0.0f;
+#pragma unroll
+                    for (int c = 0; c < 15; ++c) ep[c] = fmaf(o[r][c], d, ep[c]);
                 }
-                // The wavefront's rows j = wave + NW r (r < 38) in half-steps
-                // of FC1_ROWS / 2 rows: the next half-step's pushes are issued
-                // before the current one's returns are summed, so about
-                // 15 FC1_ROWS pushes stay in flight throughout (a row is summed
-                // once all its returns are in, rows in increasing order).
-                constexpr int HR = FC1_ROWS / 2, NR = (F1 + NW - 1) / NW;
-                static_assert(NR % (2 * HR) == HR, "38 rows: pairs of half-steps and a last half-step");
-                float oldA[HR][15], oldB[HR][15];
-                auto issue = [&](float (&o)[HR][15], int r0) {
-#pragma unroll
-                    for (int r = 0; r < HR; ++r) {
-                        const int jr = wave + NW * (r0 + r);
-                        const float d = (jr < F1) ? sm.dh[jr] : 0.0f;
-#pragma unroll
-                        for (int c = 0; c < 15; ++c) {
-                            const int i = lane + 64 * c;
-                            o[r][c] = (jr < F1 && i < NF1) ? push.with_old(DF1 + jr * NF1S + i, OF1 + jr * NF1 + i, d * xv[c])
-                                                           : 0.0f;
-                        }
-                    }
-                };
-                auto consume = [&](const float (&o)[HR][15], int r0) {
-#pragma unroll
-                    for (int r = 0; r < HR; ++r) {
-                        const int jr = wave + NW * (r0 + r);
-                        const float d = (jr < F1) ? sm.dh[jr] : 0.0f;
-#pragma unroll
-                        for (int c = 0; c < 15; ++c) ep[c] = fmaf(o[r][c], d, ep[c]);
-                    }
-                };
-                // (scheduling barriers keep the half-steps in this order)
-                issue(oldA, 0);
+            };
+            // (scheduling barriers keep the half-steps in this order)
+            issue(oldA, 0);
 #pragma unroll 1
-                for (int r0 = 0; r0 + 2 * HR < NR; r0 += 2 * HR) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue(oldB, r0 + HR);
-                    __builtin_amdgcn_sched_barrier(0);
-                    consume(oldA, r0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue(oldA, r0 + 2 * HR);
-                    __builtin_amdgcn_sched_barrier(0);
-                    consume(oldB, r0 + HR);
-                }
+            for (int r0 = 0; r0 + 2 * HR < NR; r0 += 2 * HR) {
                 __builtin_amdgcn_sched_barrier(0);
-                consume(oldA, NR - HR);
-                float *part = sm.pushbuf[0];  // [wavefront][input]
+                issue(oldB, r0 + HR);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(oldA, r0);
+                __builtin_amdgcn_sched_barrier(0);
+                issue(oldA, r0 + 2 * HR);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(oldB, r0 + HR);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            consume(oldA, NR - HR);
+            float *part = sm.pushbuf[0];  // [wavefront][input]
 #pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    if (i < NF1) part[wave * NF1 + i] = ep[c];
-                }
+            for (int c = 0; c < 15; ++c) {
+                int i = lane + 64 * c;
+                if (i < NF1) part[wave * NF1 + i] = ep[c];
             }
         }
         __syncthreads();
         // e3 = the partial sums in wavefront order (training); pool2
         // backward -> conv3 output deltas d3[o][4P + w]; clear s2
-        if constexpr (MODE != kForwardBackward) {
+        {
             const float *part = sm.pushbuf[0];
             for (int q = tid; q < NF1; q += NT)
                 sm.e3[q] = ((part[q] + part[NF1 + q]) + part[2 * NF1 + q]) + part[3 * NF1 + q];
@@ -754,25 +702,6 @@ __global__ void __launch_bounds__(NT, 1) fused_large_kernel(WorkArgs a) {
         }
         __syncthreads();
 
-        // batched gradient (frozen weights, a.stash): this sample's conv3
-        // output deltas and conv3 inputs go to HBM, and the conv3 weight
-        // gradient is contracted over the batch afterwards; the bias
-        // gradient is pushed as usual
-        if (MODE == kForwardBackward && a.stash) {
-            float *d3s = a.stash + idx * (C3 * M3);
-            float *y2s = a.stash + a.n * (int64_t)(C3 * M3) + idx * (C2 * NY2);
-            for (int t = tid; t < C3 * M3; t += NT) {
-                const int o = t / M3, m = t - o * M3;
-                d3s[t] = sm.d3[o * M3P + m];
-            }
-            for (int t = tid; t < C2 * NY2; t += NT) y2s[t] = sm.y2[t];
-            if (tid < C3) {
-                float g4[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int m = 0; m < M3; ++m) g4[m & 3] += sm.d3[tid * M3P + m];
-                push(DB3 + tid, OB3 + tid, (g4[0] + g4[1]) + (g4[2] + g4[3]));
-            }
-        } else
         // conv3 weight gradient G[o][k] = sum_m d3[o][m] y2col[m][k], pushed.
         // Maps 0..95 on 32x32x2 tiles: element r of a tile holds maps
         // 8(r/4) + r%4 and that + 4 at 32 consecutive k, so a push

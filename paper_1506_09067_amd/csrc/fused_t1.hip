@@ -554,8 +554,8 @@ __global__ void __launch_bounds__(NT, 1) fused_t1_kernel(WorkArgs a) {
         push.mode = MODE;
         push.params = a.params;
         push.neg_lr = -a.lr;
-        push.each = a.grad_each ? a.grad_each + idx * (int64_t)NPARAM : nullptr;
-        push.part = a.grad_part ? a.grad_part + (int64_t)blockIdx.x * NPARAM : nullptr;
+        push.each = nullptr;
+        push.part = nullptr;
 
         // output layer: E = 1/2 sum (y - t)^2, delta = (y - t) f'(z)
         if (tid < 64) {
@@ -568,6 +568,12 @@ __global__ void __launch_bounds__(NT, 1) fused_t1_kernel(WorkArgs a) {
             }
             e = wave_sum(e);
             if (tid == 0 && a.loss) a.loss[idx] = 0.5f * e;
+        }
+        if constexpr (MODE == kForwardBackward) {
+            // outputs and losses at frozen weights, the bits of a training pass at
+            // lr 0 (gradients are the batched engine's)
+            __syncthreads();
+            continue;
         }
         __syncthreads();
         // FC2 backward data (pre-update weights)
@@ -594,101 +600,51 @@ __global__ void __launch_bounds__(NT, 1) fused_t1_kernel(WorkArgs a) {
         }
         if (tid < F2) push(DBF2 + tid, OBF2 + tid, sm.dout[tid]);
         if (tid < F1) push(DBF1 + tid, OBF1 + tid, sm.dh[tid]);
-        if constexpr (MODE == kForwardBackward) {
-            // frozen weights: read them (16-byte loads, ten rows per batch,
-            // the next batch requested while this one is summed), then push
-            if (tid < NF1 / 4) {
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-                f4 wa[10], wb[10];
-                auto load = [&](f4 (&w)[10], int j0) {
+        {
+            float xv[15], ep[15];
 #pragma unroll
-                    for (int jj = 0; jj < 10; ++jj)
-                        w[jj] = *(const f4 *)(W + DF1 + (j0 + jj) * NF1S + 4 * tid);
-                };
-                auto comp = [&](const f4 (&w)[10], int j0) {
-#pragma unroll
-                    for (int jj = 0; jj < 10; ++jj) {
-                        float d = sm.dh[j0 + jj];
-                        acc.x = fmaf(w[jj].x, d, acc.x);
-                        acc.y = fmaf(w[jj].y, d, acc.y);
-                        acc.z = fmaf(w[jj].z, d, acc.z);
-                        acc.w = fmaf(w[jj].w, d, acc.w);
-                    }
-                };
-                load(wa, 0);
-                for (int j0 = 0; j0 < F1; j0 += 20) {
-                    if (j0 + 10 < F1) load(wb, j0 + 10);
-                    comp(wa, j0);
-                    if (j0 + 10 < F1) {
-                        if (j0 + 20 < F1) load(wa, j0 + 20);
-                        comp(wb, j0 + 10);
-                    }
-                }
-                *(f4 *)(sm.e3 + 4 * tid) = acc;
+            for (int c = 0; c < 15; ++c) {
+                int i = lane + 64 * c;
+                xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
+                ep[c] = 0.0f;
             }
-            {
-                float xv[15];
+            // FC1_ROWS rows per step: 15 FC1_ROWS pushes in flight before
+            // their returns are used (a wavefront's rows are still summed
+            // in increasing order)
+            for (int j = wave; j < F1; j += FC1_ROWS * NW) {
+                float old[FC1_ROWS][15], dr[FC1_ROWS];
 #pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
-                }
-                for (int j = wave; j < F1; j += NW) {
-                    const float d = sm.dh[j];
+                for (int r = 0; r < FC1_ROWS; ++r) {
+                    const int jr = j + r * NW;
+                    dr[r] = (jr < F1) ? sm.dh[jr] : 0.0f;
+                    if (jr < F1) {
 #pragma unroll
-                    for (int c = 0; c < 15; ++c) {
-                        int i = lane + 64 * c;
-                        if (i < NF1) push(DF1 + j * NF1S + i, OF1 + j * NF1 + i, d * xv[c]);
-                    }
-                }
-            }
-        } else {
-            {
-                float xv[15], ep[15];
-#pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    xv[c] = (i < NF1) ? sm.p3[i] : 0.0f;
-                    ep[c] = 0.0f;
-                }
-                // FC1_ROWS rows per step: 15 FC1_ROWS pushes in flight before
-                // their returns are used (a wavefront's rows are still summed
-                // in increasing order)
-                for (int j = wave; j < F1; j += FC1_ROWS * NW) {
-                    float old[FC1_ROWS][15], dr[FC1_ROWS];
-#pragma unroll
-                    for (int r = 0; r < FC1_ROWS; ++r) {
-                        const int jr = j + r * NW;
-                        dr[r] = (jr < F1) ? sm.dh[jr] : 0.0f;
-                        if (jr < F1) {
-#pragma unroll
-                            for (int c = 0; c < 15; ++c) {
-                                int i = lane + 64 * c;
-                                old[r][c] = (i < NF1) ? push.with_old(DF1 + jr * NF1S + i, OF1 + jr * NF1 + i, dr[r] * xv[c])
-                                                      : 0.0f;
-                            }
-                        } else {
-#pragma unroll
-                            for (int c = 0; c < 15; ++c) old[r][c] = 0.0f;
+                        for (int c = 0; c < 15; ++c) {
+                            int i = lane + 64 * c;
+                            old[r][c] = (i < NF1) ? push.with_old(DF1 + jr * NF1S + i, OF1 + jr * NF1 + i, dr[r] * xv[c])
+                                                  : 0.0f;
                         }
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 15; ++c) old[r][c] = 0.0f;
                     }
-#pragma unroll
-                    for (int r = 0; r < FC1_ROWS; ++r)
-#pragma unroll
-                        for (int c = 0; c < 15; ++c) ep[c] = fmaf(old[r][c], dr[r], ep[c]);
                 }
-                float *part = sm.fcpart;  // [wavefront][input]
 #pragma unroll
-                for (int c = 0; c < 15; ++c) {
-                    int i = lane + 64 * c;
-                    if (i < NF1) part[wave * NF1 + i] = ep[c];
-                }
+                for (int r = 0; r < FC1_ROWS; ++r)
+#pragma unroll
+                    for (int c = 0; c < 15; ++c) ep[c] = fmaf(old[r][c], dr[r], ep[c]);
+            }
+            float *part = sm.fcpart;  // [wavefront][input]
+#pragma unroll
+            for (int c = 0; c < 15; ++c) {
+                int i = lane + 64 * c;
+                if (i < NF1) part[wave * NF1 + i] = ep[c];
             }
         }
         __syncthreads();
         // e3 = the partial sums in wavefront order (training); pool2
         // backward -> conv3 output deltas d3[o][4P + w]; clear s2
-        if constexpr (MODE != kForwardBackward) {
+        {
             const float *part = sm.fcpart;
             for (int q = tid; q < NF1; q += NT)
                 sm.e3[q] = ((part[q] + part[NF1 + q]) + part[2 * NF1 + q]) + part[3 * NF1 + q];

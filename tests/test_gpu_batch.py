@@ -1,0 +1,136 @@
+"""The batched frozen-weight engine against the oracle, on MI355X.
+
+Layer lists at the edges of its kernels: maps that are no multiple of the 4, 8
+and 16 that operands come in, no pooling and windows of 2, 3 and 5, more than 64
+output maps (long K of the backward pass), more than 160 (several row groups of a
+weight gradient), K long enough to be split over the wavefronts, a map whose
+positions go through the weight gradient in bands, an output layer with several
+positions, a fully connected layer after another.  Sample counts around a
+workgroup's.  Outputs, losses, per-sample gradients and their sum at the 1e-4 of
+tests/_compare.py (float32 sums of up to a few thousand products are within 1e-5);
+a sample whose pooling has a near-tie in float64 may route its error differently.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_1506_09067_amd import workloads as wl
+
+from . import _oracle_par as par
+from ._compare import assert_close, close_report
+
+pytestmark = pytest.mark.gpu
+
+NEAR_TIE = 1e-5
+CONV, POOL, FC = orc.CONV, orc.MAXPOOL, orc.FC
+
+# name: (input side, layer list)
+NETS = {
+    "one_conv": (6, [(CONV, 3, 6)]),
+    "conv_positions_out": (7, [(CONV, 5, 3), (CONV, 2, 2)]),
+    "odd_maps": (12, [(CONV, 7, 3), (POOL, 0, 2), (CONV, 13, 2), (FC, 9, 0), (FC, 3, 0)]),
+    "pool3_pool2": (20, [(CONV, 18, 3), (POOL, 0, 3), (CONV, 33, 3), (POOL, 0, 2), (FC, 17, 0)]),
+    "long_k_wide": (14, [(CONV, 24, 3), (CONV, 100, 5), (POOL, 0, 2), (FC, 40, 0), (FC, 10, 0)]),
+    "many_maps": (8, [(CONV, 9, 3), (CONV, 170, 3), (POOL, 0, 2), (FC, 6, 0)]),
+    "bands": (29, [(CONV, 20, 4), (CONV, 50, 5), (POOL, 0, 2), (FC, 10, 0)]),
+    "pool5_fc_fc": (29, [(CONV, 6, 5), (POOL, 0, 5), (FC, 20, 0), (FC, 10, 0)]),
+    "wide_fc": (9, [(CONV, 4, 2), (FC, 180, 0), (FC, 70, 0), (FC, 10, 0)]),
+}
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1506_09067_amd import chaos
+    chaos.lib()
+    return torch, chaos
+
+
+@pytest.mark.parametrize("n", [1, 5, 37])
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_batched_engine_against_oracle(env, name, n):
+    torch, chaos = env
+    hw, layers = NETS[name]
+    p = wl.init_params(layers, in_h=hw, in_w=hw)
+    net = chaos.Net(layers, p, in_h=hw, in_w=hw)
+    x = wl.images(n, 11, hw * hw)
+    y = (wl.uniform_labels(n, 11) % min(net.n_out, 10)).astype(np.int32)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    print(f"{name} n={n}", flush=True)
+    out, loss = torch.empty(n, net.n_out, device="cuda"), torch.empty(n, device="cuda")
+    each = torch.full((n, net.n_params), float("nan"), device="cuda")
+    gsum = torch.full((net.n_params,), float("nan"), device="cuda")
+    net.forward_backward(xd, yd, out=out, loss=loss, grad_sum=gsum, grad_each=each)
+    ev = torch.empty(n, net.n_out, device="cuda")
+    wrong = net.evaluate(xd, yd, out=ev)
+    again = torch.empty_like(gsum)
+    net.forward_backward_noalloc(xd, yd, grad_sum=again)
+    torch.cuda.synchronize()
+    refs = par.forward_backward(layers, p, x, y, range(n), in_h=hw, in_w=hw)
+    out, loss, each = out.cpu().numpy(), loss.cpu().numpy(), each.cpu().double().numpy()
+    assert int(wrong.item()) == int(np.sum(np.argmax(ev.cpu().numpy(), axis=1) != y))
+    skipped = []
+    for i, r in enumerate(refs):
+        assert_close(out[i], r["out"], what=f"{name} out[{i}]")
+        assert_close(ev[i].cpu().numpy(), r["out"], what=f"{name} evaluate out[{i}]")
+        assert_close([loss[i]], [r["loss"]], what=f"{name} loss[{i}]")
+        ok, msg = close_report(each[i], r["grad"])
+        if not ok and r["min_gap"] < NEAR_TIE:
+            skipped.append(i)
+            continue
+        assert ok, f"{name} grad[{i}]: {msg}"
+    assert len(skipped) <= 1, skipped
+    G = np.sum([r["grad"] for i, r in enumerate(refs) if i not in skipped], axis=0)
+    for what, g in (("forward_backward", gsum), ("noalloc", again)):
+        assert_close(g.cpu().double().numpy() - each[skipped].sum(0), G, what=f"{name} gradient sum, {what}")
+
+
+@pytest.mark.parametrize("name", ["large_table1", "medium"])
+def test_batched_engine_in_several_passes(env, name):
+    """More samples than the no-allocation workspace holds at a time: outputs
+    do not depend on the pass a sample is in, sums add up over the passes."""
+    torch, chaos = env
+    layers = wl.NETS[name]
+    net = chaos.Net(layers, wl.init_params(layers))
+    n = 3001 if name == "medium" else 1301
+    x, y = wl.batch_set(n)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    res = []
+    for call in (net.forward_backward, net.forward_backward_noalloc):
+        o, l, g = (torch.empty(n, net.n_out, device="cuda"), torch.empty(n, device="cuda"),
+                   torch.empty(net.n_params, device="cuda"))
+        call(xd, yd, out=o, loss=l, grad_sum=g)
+        res.append((o, l, g))
+    ev = torch.empty(n, net.n_out, device="cuda")
+    net.evaluate(xd, yd, out=ev)
+    torch.cuda.synchronize()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert torch.equal(ev, res[0][0])
+    assert_close(res[1][2].cpu().numpy(), res[0][2].cpu().double().numpy(), what=f"{name} sums in two pass sizes")
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_batched_engine_with_pixels_that_are_not_finite(env, value):
+    """A pixel that is not finite stays in its own sample: the others' outputs
+    are unchanged, an infinite pixel saturates as in the per-sample kernel."""
+    torch, chaos = env
+    layers = wl.NETS["large"]
+    net = chaos.Net(layers, wl.init_params(layers))
+    x, _ = wl.batch_set(300)
+    y = torch.zeros(300, dtype=torch.int32, device="cuda")
+    xd = torch.from_numpy(x).cuda()
+    ref = torch.empty(300, 10, device="cuda")
+    net.evaluate(xd, y, out=ref)
+    xd[7, 400] = value
+    out, own = torch.empty_like(ref), torch.empty(1, 10, device="cuda")
+    net.evaluate(xd, y, out=out)
+    net.evaluate(xd[7:8].contiguous(), y[:1], out=own)
+    torch.cuda.synchronize()
+    keep = [i for i in range(300) if i != 7]
+    assert torch.equal(out[keep], ref[keep])
+    if value == float("inf"):
+        assert_close(out[7].cpu().numpy(), own[0].cpu().double().numpy(), what="saturated sample")
+    else:
+        assert torch.isnan(out[7]).all() == torch.isnan(own[0]).all()
