@@ -1576,7 +1576,8 @@ bool pick_wgrad(const Stage &g, bool first, int64_t n, bool each, WgradCfg &c) {
         c.upc = c.NB;
         c.chunks = n;
     } else {
-        c.chunks = std::max<int64_t>(1, std::min(c.units, cdiv(target, blocks_yz)));
+        // at most one round of workgroups: a chunk more would take a second one
+        c.chunks = std::max<int64_t>(1, std::min(c.units, target / blocks_yz));
         c.upc = cdiv(c.units, c.chunks);
         c.chunks = cdiv(c.units, c.upc);
     }
