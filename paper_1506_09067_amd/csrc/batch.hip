@@ -211,10 +211,10 @@ __device__ __forceinline__ void store_tile(f4 t, int row0, int lg, int rows, int
 
 // The outputs of the workgroup's pre-activation map z [row][on] in LDS, maps
 // o0 .. o0 + on.
-__device__ __forceinline__ void store_map(const float *z, int ns, int on, FastDiv fon, int o0, const RowDiv &d, int p,
+__device__ __forceinline__ void store_map(const float *z, int npool, int on, FastDiv fon, int o0, const RowDiv &d, int p,
                                           int O, const float *__restrict__ bias, float *__restrict__ y,
                                           uint8_t *__restrict__ arg) {
-    const int items = ns * d.Pp * on;
+    const int items = npool * on;
     for (int t = threadIdx.x; t < items; t += NT_) {
         const int sp = fdiv(t, fon), o = t - sp * on;
         const int s = fdiv(sp, d.fPp), P = sp - s * d.Pp, py = fdiv(P, d.fWp), px = P - py * d.Wp;
@@ -350,7 +350,7 @@ __global__ void __launch_bounds__(NT_) conv_first_kernel(FirstArgs a) {
     }
     if constexpr (POOL == 0) {
         __syncthreads();
-        store_map(z, ns, a.O, a.fO, 0, a.d, a.p, a.O, a.params + a.b_off, a.y + s0 * a.nout,
+        store_map(z, ns * a.d.Pp, a.O, a.fO, 0, a.d, a.p, a.O, a.params + a.b_off, a.y + s0 * a.nout,
                   a.arg ? a.arg + s0 * a.nout : nullptr);
     } else if constexpr (POOL == 2) {
         // every lane on an output: a tile's 16 columns hold 5 to 20 maps
@@ -373,29 +373,34 @@ struct FwdArgs {
     float *y;
     uint8_t *arg;
     int64_t n;
-    int S, HW, W, C, C8, st, K, T, vec;
-    int O, p, nout;
+    int S, NB, RB;                 // samples per workgroup; bands of RB output rows (NB > 1: S = 1)
+    int HW, in_hw;                 // positions staged, and in memory, per sample
+    int W, C, C8, st, K, T, vec;
+    int Ho, O, p, nout;
     int KS, CT, ctb;               // K steps, column tiles, column tiles per workgroup
     int tab, red, z, alias;        // LDS offsets in bytes; alias: red and z overlay the inputs
-    RowDiv d;
-    FastDiv fC8, fK, fon, fon_last;  // maps of a workgroup, of the last one
+    RowDiv d;                      // of a band
+    FastDiv fC8, fK, fNB, fon, fon_last;  // maps of a workgroup, of the last one
 };
 
+// tilings of at most 16 tiles fit 256 registers: two workgroups to a CU
 template <int MT, int NT, int WK, int POOL>
-__global__ void __launch_bounds__(NT_, 1) conv_fwd_kernel(FwdArgs a) {
+__global__ void __launch_bounds__(NT_, MT * NT <= 16 ? 2 : 1) conv_fwd_kernel(FwdArgs a) {
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t s0 = (int64_t)blockIdx.x * a.S;
-    const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S);
+    const int sg = fdiv(blockIdx.x, a.fNB), y0 = (blockIdx.x - sg * a.NB) * a.RB;
+    const int64_t s0 = (int64_t)sg * a.S;
+    const int ns = (int)((a.n - s0 < a.S) ? a.n - s0 : a.S), rb = (a.Ho - y0 < a.RB) ? a.Ho - y0 : a.RB;
     int *tab = (int *)(smem + a.tab);  // byte offset of chunk q from a row's position
     for (int q = tid; q < 4 * a.KS; q += NT_) {
         const int t = fdiv(q, a.fC8), c8 = q - t * a.C8, u = fdiv(t, a.fK);
         tab[q] = (t < a.T) ? (u * a.W + (t - u * a.K)) * a.st + c8 * 48 : 0;
     }
     {
-        const float *src = a.in + s0 * a.HW * a.C;
-        const int items = ns * a.HW * a.C8;
+        // (several samples are whole ones, staged as they lie in memory)
+        const float *src = a.in + (s0 * a.in_hw + y0 * a.W) * a.C;
+        const int items = ((ns - 1) * a.HW + (rb + a.K - 1) * a.W) * a.C8;
         constexpr int U = 8;  // positions in flight per thread
         for (int i0 = tid; i0 < items; i0 += U * NT_) {
             float v[U][8];
@@ -421,13 +426,14 @@ __global__ void __launch_bounds__(NT_, 1) conv_fwd_kernel(FwdArgs a) {
     __syncthreads();
     const int ctile0 = blockIdx.y * a.ctb, ctn = (a.CT - ctile0 < a.ctb) ? a.CT - ctile0 : a.ctb;
     const int o0 = 16 * ctile0, on = (a.O - o0 < 16 * ctn) ? a.O - o0 : 16 * ctn;  // this workgroup's maps
-    const int rows = ns * a.d.P, RG = (rows + 16 * MT - 1) / (16 * MT), CG = (ctn + NT - 1) / NT;
+    const int rows = (ns - 1) * a.d.P + rb * a.d.Wo, RG = (rows + 16 * MT - 1) / (16 * MT), CG = (ctn + NT - 1) / NT;
     float *z = (float *)(smem + a.z);
     const int kper = (WK == 1) ? a.KS : (a.KS + 3) / 4;
     const int k0 = (WK == 1) ? 0 : wave * kper, k1 = (k0 + kper < a.KS) ? k0 + kper : a.KS;
     const int jobs = RG * CG;
-    float *yg = a.y + s0 * a.nout + o0;
-    uint8_t *ag = a.arg ? a.arg + s0 * a.nout + o0 : nullptr;
+    const int64_t out0 = s0 * a.nout + (int64_t)(POOL == 2 ? y0 / 2 : POOL == 1 ? y0 : y0 / a.p) * a.d.Wp * a.O + o0;
+    float *yg = a.y + out0;
+    uint8_t *ag = a.arg ? a.arg + out0 : nullptr;
     // (with alias there is one job per wavefront, and every wavefront passes the
     // barriers once; without, the barriers of WK = 4 are in a uniform loop)
     for (int job = (WK == 1) ? wave : 0; job < jobs || a.alias; job += (WK == 1) ? 4 : 1) {
@@ -574,7 +580,7 @@ __global__ void __launch_bounds__(NT_, 1) conv_fwd_kernel(FwdArgs a) {
     }
     if constexpr (POOL == 0) {
         __syncthreads();
-        store_map(z, ns, on, (int)blockIdx.y == (int)gridDim.y - 1 ? a.fon_last : a.fon, o0, a.d, a.p, a.O, a.bias, yg - o0,
+        store_map(z, (ns - 1) * a.d.Pp + rb / a.p * a.d.Wp, on, (int)blockIdx.y == (int)gridDim.y - 1 ? a.fon_last : a.fon, o0, a.d, a.p, a.O, a.bias, yg - o0,
                   ag ? ag - o0 : nullptr);
     }
 }
@@ -1323,17 +1329,18 @@ bool first_fits(const Stage &g, int S, FirstArgs &a, int64_t &bytes) {
 bool split_k(const Stage &g) { return g.KS >= 24; }
 
 struct FwdCfg {
-    int mt, nt, S, ctb, alias;
+    int mt, nt, S, NB, RB, ctb, alias;
     int64_t bytes;
     int tab, red, z;
 };
 
 bool fwd_fits(const Stage &g, FwdCfg &c) {
-    const int wk = split_k(g) ? 4 : 1;
-    const int64_t in = cdiv((int64_t)c.S * g.H * g.W * g.st, 16) * 16, tab = 16 * (int64_t)g.KS;
+    const int wk = split_k(g) ? 4 : 1, om = std::min(g.O, 16 * c.ctb);
+    const int64_t rows = (int64_t)c.S * c.RB * g.Wo;
+    const int64_t in = cdiv((int64_t)c.S * (c.RB + g.K - 1) * g.W * g.st, 16) * 16, tab = 16 * (int64_t)g.KS;
     const int64_t red = wk == 4 ? (int64_t)2 * c.mt * c.nt * 1024 : 0;
-    const int64_t z = pool_kind(g) == 0 ? (int64_t)c.S * g.P * std::min(g.O, 16 * c.ctb) * 4 : 0;
-    const int64_t jobs = cdiv((int64_t)c.S * g.P, 16 * c.mt) * cdiv(c.ctb, c.nt);
+    const int64_t z = pool_kind(g) == 0 ? rows * om * 4 : 0;
+    const int64_t jobs = cdiv(rows, 16 * c.mt) * cdiv(c.ctb, c.nt);
     c.alias = jobs <= (wk == 4 ? 1 : 4);
     c.tab = (int)in;
     if (c.alias) {
@@ -1348,44 +1355,65 @@ bool fwd_fits(const Stage &g, FwdCfg &c) {
     return c.bytes <= kLds && in + tab <= kLds;
 }
 
-// tilings of each kind, largest first
-constexpr int kTile1[][2] = {{8, 4}, {8, 3}, {8, 1}, {2, 2}};
+// tilings of each kind
+constexpr int kTile1[][2] = {{4, 4}, {4, 3}, {4, 1}, {2, 2}};
 constexpr int kTile4[][2] = {{5, 7}, {3, 7}, {2, 5}, {4, 1}};
 
-// Picks the samples per workgroup, the tiling and the column tiles per
-// workgroup: the least estimated time, from the matrix instructions of the
-// busiest wavefront, the staging and epilogue of a workgroup and the rounds
-// of workgroups over the compute units.
+// Estimated time of a layer in cycles: the matrix instructions of the busiest
+// wavefront, the staging and epilogue of a workgroup, the rounds of workgroups
+// over the compute units.
+double fwd_cost(const Stage &g, int64_t n, const FwdCfg &c) {
+    const bool k4 = split_k(g);
+    const int om = std::min(g.O, 16 * c.ctb);
+    const double conv = (double)c.S * c.RB * g.Wo * om;  // outputs of a workgroup before pooling
+    const double rg = (double)cdiv((int64_t)c.S * c.RB * g.Wo, 16 * c.mt), cg = (double)cdiv(c.ctb, c.nt);
+    const double job =
+        (k4 ? cdiv(g.KS, 4) : g.KS) * (c.mt * c.nt * 130.0 + 100.0) + (k4 ? 60.0 * c.mt * c.nt + 1500 : 0);
+    const double mm = job * (k4 ? rg * cg : (double)cdiv((int64_t)(rg * cg), 4));
+    const double stage = 4000 + (double)c.S * (c.RB + g.K - 1) * g.W * g.C8 * 5;
+    const double epi = 1500 + conv * (pool_kind(g) == 1 ? 0.9 : pool_kind(g) == 2 ? 0.3 : 0.8);
+    const double blocks = (double)cdiv(n, c.S) * c.NB * cdiv(g.CT, c.ctb);
+    const bool two = c.mt * c.nt <= 16 && c.bytes <= kLds / 2 && blocks > kCus;
+    // two workgroups on a CU share its matrix cores, one's staging and epilogue
+    // under the other's products
+    const double pair = two ? std::max(2 * mm + 1000, mm + stage + epi) : mm + stage + epi;
+    return std::ceil(blocks / (two ? 2 * kCus : kCus)) * pair;
+}
+
+// Picks the samples (or the band of one) per workgroup, the tiling and the
+// column tiles per workgroup.
 bool pick_fwd(const Stage &g, int64_t n, FwdCfg &best) {
     const bool k4 = split_k(g);
     double least = 0;
     bool found = false;
-    for (int t = 0; t < 4; ++t) {
+    auto consider = [&](const FwdCfg &c) {
+        const double cost = fwd_cost(g, n, c);
+        if (!found || cost < least) {
+            least = cost;
+            best = c;
+            found = true;
+        }
+    };
+    const int nt1 = sizeof(kTile1) / sizeof(kTile1[0]), nt4 = sizeof(kTile4) / sizeof(kTile4[0]);
+    for (int t = 0; t < (k4 ? nt4 : nt1); ++t) {
         FwdCfg c{};
         c.mt = k4 ? kTile4[t][0] : kTile1[t][0];
         c.nt = k4 ? kTile4[t][1] : kTile1[t][1];
         for (int cgs = 1; cgs <= g.CT; cgs *= 2) {
             c.ctb = (int)cdiv(g.CT, cgs);
             const int64_t smax = std::min<int64_t>(n, 64);
+            c.NB = 1;
+            c.RB = g.Ho;
             for (c.S = 1; c.S <= smax; ++c.S) {
                 if (!fwd_fits(g, c)) break;
-                const double rg = (double)cdiv((int64_t)c.S * g.P, 16 * c.mt), cg = (double)cdiv(c.ctb, c.nt);
-                const double job = (k4 ? cdiv(g.KS, 4) : g.KS) * (c.mt * c.nt * 96.0 + 60.0) +
-                                   (k4 ? 40.0 * c.mt * c.nt + 400 : 0);
-                const double mm = job * (k4 ? rg * cg : (double)cdiv((int64_t)(rg * cg), 4));
-                const double stage = 1500 + (double)c.S * g.H * g.W * g.C8 * 0.9;
-                const double epi = 600 + (double)c.S * g.P * std::min(g.O, 16 * c.ctb) * 0.12 +
-                                   (double)c.S * g.Pp * std::min(g.O, 16 * c.ctb) * 0.5;
-                const int64_t blocks = cdiv(n, c.S) * cdiv(g.CT, c.ctb);
-                const int per_cu = (int)std::max<int64_t>(1, std::min<int64_t>(2, kLds / std::max<int64_t>(c.bytes, 1)));
-                // two workgroups on a CU share its matrix cores; staging and epilogue overlap
-                const double rounds = (double)cdiv(blocks, (int64_t)kCus * per_cu);
-                const double cost = rounds * (per_cu == 2 ? std::max(2 * mm, mm + stage + epi) : mm + stage + epi);
-                if (!found || cost < least) {
-                    least = cost;
-                    best = c;
-                    found = true;
-                }
+                consider(c);
+            }
+            if (k4) continue;
+            c.S = 1;
+            for (int nb = 2; nb <= g.Hp && nb <= 16; ++nb) {
+                c.RB = (int)cdiv(g.Hp, nb) * g.p;
+                c.NB = (int)cdiv(g.Ho, c.RB);
+                if (fwd_fits(g, c)) consider(c);
             }
         }
     }
@@ -1401,7 +1429,7 @@ void launch_fwd(const FwdArgs &a, const FwdCfg &c, int pool, dim3 grid, hipStrea
 
 hipError_t run_fwd(const FwdArgs &a, const FwdCfg &c, bool k4, int pool, dim3 grid, hipStream_t s) {
 #define CHAOS_FWD(M, N, K)                                    if (c.mt == M && c.nt == N && k4 == (K == 4)) {               launch_fwd<M, N, K>(a, c, pool, grid, s);                 return hipGetLastError();                             }
-    CHAOS_FWD(8, 4, 1) CHAOS_FWD(8, 3, 1) CHAOS_FWD(8, 1, 1) CHAOS_FWD(2, 2, 1)
+    CHAOS_FWD(4, 4, 1) CHAOS_FWD(4, 3, 1) CHAOS_FWD(4, 1, 1) CHAOS_FWD(2, 2, 1)
     CHAOS_FWD(5, 7, 4) CHAOS_FWD(3, 7, 4) CHAOS_FWD(2, 5, 4) CHAOS_FWD(4, 1, 4)
 #undef CHAOS_FWD
     return hipErrorInvalidValue;
@@ -1814,8 +1842,12 @@ hipError_t launch_forward(const BatchPlan &plan, const BatchWork &w, const Batch
         a.arg = arg;
         a.n = n;
         a.S = f.S;
-        a.HW = g.H * g.W;
+        a.NB = f.NB;
+        a.RB = f.RB;
+        a.HW = (f.RB + g.K - 1) * g.W;
+        a.in_hw = g.H * g.W;
         a.W = g.W;
+        a.Ho = g.Ho;
         a.C = g.C;
         a.C8 = g.C8;
         a.st = g.st;
@@ -1833,12 +1865,14 @@ hipError_t launch_forward(const BatchPlan &plan, const BatchWork &w, const Batch
         a.z = f.z;
         a.alias = f.alias;
         a.fC8 = fast_div(g.C8);
-        a.d = row_div(g);
+        a.d = RowDiv{f.RB * g.Wo,           g.Wo,           f.RB / g.p * g.Wp,           g.Wp,
+                     fast_div(f.RB * g.Wo), fast_div(g.Wo), fast_div(f.RB / g.p * g.Wp), fast_div(g.Wp)};
         a.fK = fast_div(g.K);
+        a.fNB = fast_div(f.NB);
         const int gy = (int)cdiv(g.CT, f.ctb);
         a.fon = fast_div(std::min(g.O, 16 * f.ctb));
         a.fon_last = fast_div(g.O - 16 * f.ctb * (gy - 1));
-        hipError_t e = run_fwd(a, f, split_k(g), pool_kind(g), dim3((unsigned)cdiv(n, f.S), (unsigned)gy), s);
+        hipError_t e = run_fwd(a, f, split_k(g), pool_kind(g), dim3((unsigned)(cdiv(n, f.S) * f.NB), (unsigned)gy), s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
