@@ -11,7 +11,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libchaos.so")
-SOURCES = ["worker.hip", "fused_large.hip", "fused_t1.hip", "fused_cpcp.hip", "batch.hip",
+SOURCES = ["worker.hip", "worker_lds.hip", "fused_large.hip", "fused_t1.hip", "fused_cpcp.hip", "batch.hip",
            "chaos_api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

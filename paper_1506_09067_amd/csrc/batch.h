@@ -89,4 +89,22 @@ CHAOS_WEAK int64_t batch_part_floats(const BatchPlan &plan, int64_t n);
 CHAOS_WEAK int64_t batch_part_min(const BatchPlan &plan);
 CHAOS_WEAK hipError_t launch_batch(const BatchPlan &plan, const BatchWork &w, const BatchCall &c, hipStream_t s);
 
+// ---- training worker with its per-sample state in LDS (worker_lds.hip) ----
+// One convolution or fully connected layer with the pooling layer after it;
+// activations are [map][position], LDS offsets in floats.
+struct LdsStage {
+    int fc, C, H, W, O, K, Ho, Wo, p, Hp, Wp;
+    int w_off, b_off;
+    int y_off, arg_off, tab_off;  // outputs, argmax bytes, offsets of (map, kernel) in the input
+};
+struct LdsPlan {
+    int n, in_size, n_out;
+    int z_off, red_off, e_off[2];  // conv outputs / framed deltas; partial tiles; errors
+    int64_t bytes;
+    LdsStage s[kMaxLayers];
+};
+CHAOS_WEAK bool worker_lds_plan(const Net &net, LdsPlan &plan);
+CHAOS_WEAK int worker_lds_blocks_per_cu(const LdsPlan &plan);
+CHAOS_WEAK hipError_t launch_worker_lds(int mode, const LdsPlan &plan, const WorkArgs &a, int grid, hipStream_t s);
+
 } // namespace chaos

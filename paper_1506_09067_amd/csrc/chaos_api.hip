@@ -47,6 +47,8 @@ struct chaos_net {
     float *replicas = nullptr;    // [n_replicas][device floats]
     int32_t *rep_counter = nullptr;  // [n_replicas]
     int delay_max_workers = 0;    // resident workers of the delayed-push kernel (0 = none)
+    chaos::LdsPlan lds{};         // the LDS-resident training worker of a net without a fused kernel
+    int lds_workers = 0;          // its resident workers (0: it does not serve this net)
     chaos::BatchPlan plan;        // how the batched engine serves this net (plan.ok: it does)
     uint16_t *pack = nullptr;     // its weights in operand order
     void *act = nullptr;          // its activations, allocated with the net
@@ -270,6 +272,12 @@ bool batched_gradient(const chaos_net *net, int64_t n, const float *sum, const f
     return true;
 }
 
+// Outputs and losses alone of a net without a fused kernel (those of a fused
+// one are its kernel's, a training pass's bits).
+bool batched_losses(const chaos_net *net, const float *sum, const float *each) {
+    return net->plan.ok && !net->fused && !net->t1 && !net->cpcp && !sum && !each;
+}
+
 hipError_t batch_gradient(chaos_net *net, const chaos::BatchWork &w, const float *x, const int32_t *labels, int64_t n,
                           float *out, float *loss, float *grad_sum, float *grad_each, hipStream_t s) {
     chaos::BatchCall c{};
@@ -289,6 +297,10 @@ hipError_t launch(chaos_net *net, int mode, const chaos::WorkArgs &a, int grid, 
     if (net->fused) return chaos::launch_fused_large(mode, a, grid, s);
     if (net->t1) return chaos::launch_fused_t1(mode, a, grid, s);
     if (net->cpcp) return chaos::launch_fused_cpcp(net->cpcp, mode, a, grid, s);
+    // (a racy epoch's updates of one sample are loads, adds and stores of its own
+    // wavefronts in either kernel)
+    if ((mode == chaos::kTrainAtomic || mode == chaos::kTrainRacy) && grid <= net->lds_workers)
+        return chaos::launch_worker_lds(mode, net->lds, a, grid, s);
     return chaos::launch_worker(mode, net->desc, a, grid, net->block, s);
 }
 
@@ -327,6 +339,8 @@ int chaos_create_net(int32_t in_h, int32_t in_w, const chaos_layer *layers, int3
                : net->cpcp  ? chaos::fused_cpcp_blocks_per_cu(net->cpcp)
                             : chaos::worker_blocks_per_cu(net->block);
     if (per_cu < 1) { delete net; return fail(CHAOS_EDEVICE, "occupancy query failed"); }
+    if (!net->fused && !net->t1 && !net->cpcp && chaos::worker_lds_plan && chaos::worker_lds_plan(desc, net->lds))
+        net->lds_workers = chaos::worker_lds_blocks_per_cu(net->lds) * cus;
     net->max_workers = per_cu * cus;
     net->cus = cus;
     net->delay_max_workers = net->cpcp ? chaos::fused_cpcp_delay_blocks_per_cu(net->cpcp) * cus : 0;
@@ -621,6 +635,13 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
             HIP_TRY(chaos::launch_fill_f32(grad_sum_dev, 0.0f, net->n_params, stream), "zero grad");
         return ok();
     }
+    if (batched_losses(net, grad_sum_dev, grad_each_dev)) {
+        const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
+                                                     pass_samples(net, n, net->act_bytes, false), false);
+        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
+                "forward_backward launch");
+        return ok();
+    }
     if (batched_gradient(net, n, grad_sum_dev, grad_each_dev)) {
         const int64_t samples = pass_samples(net, n, kGradBytes, true);
         const int64_t part = grad_sum_dev ? chaos::batch_part_floats(net->plan, std::min(samples, n)) : 0;
@@ -758,6 +779,13 @@ int chaos_forward_backward_noalloc(chaos_net *net, const float *x_dev, const int
     if (n == 0) {
         if (grad_sum_dev)
             HIP_TRY(chaos::launch_fill_f32(grad_sum_dev, 0.0f, net->n_params, stream), "zero grad");
+        return ok();
+    }
+    if (batched_losses(net, grad_sum_dev, grad_each_dev)) {
+        const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
+                                                     pass_samples(net, n, net->act_bytes, false), false);
+        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
+                "forward_backward launch");
         return ok();
     }
     if (batched_gradient(net, n, grad_sum_dev, grad_each_dev) &&
