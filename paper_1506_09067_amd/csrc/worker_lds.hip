@@ -34,8 +34,44 @@ __device__ __forceinline__ void step(const float (&a)[MT], float b, f4 (&acc)[MT
     for (int i = 0; i < MT; ++i) acc[i] = mfma(a[i], b, acc[i]);
 }
 
+// Fewer jobs than half the wavefronts: each job's K is split over `parts`
+// wavefronts (in multiples of four), whose partial tiles are added in order
+// through red [wavefront][MT][lane][4].
+struct KSplit {
+    int parts, job0, stride, k0, k1;
+};
+__device__ __forceinline__ KSplit split_k(int jobs, int wave, int Kt) {
+    KSplit s;
+    s.parts = jobs <= NW / 2 ? NW / jobs : 1;
+    if (s.parts == 1) return KSplit{1, wave, NW, 0, Kt};
+    const int part = wave % s.parts, per = ((Kt + 3) / 4 + s.parts - 1) / s.parts * 4;
+    s.job0 = wave / s.parts;
+    s.stride = NW;
+    s.k0 = part * per;
+    s.k1 = s.k0 + per < Kt ? s.k0 + per : Kt;
+    return s;
+}
+// sums the parts of every job: dst[col * cs + row] for row < rows, col < cols
+template <int MT>
+__device__ __forceinline__ void add_parts(const float *red, int jobs, int parts, int RG, int rows, int cols, int cs,
+                                          float *dst) {
+    for (int t = threadIdx.x; t < jobs * MT * 64; t += NT) {
+        const int lane = t & 63, it = t >> 6, job = it / MT, i = it - job * MT;
+        const float *src = red + ((job * parts * MT + i) * 64 + lane) * 4;
+        f4 v = *(const f4 *)src;
+        for (int q = 1; q < parts; ++q) v += *(const f4 *)(src + q * MT * 256);
+        const int ct = job / RG, rg = job - ct * RG, col = 16 * ct + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * (MT * rg + i) + 4 * (lane >> 4) + r;
+            if (row < rows && col < cols) dst[col * cs + row] = v[r];
+        }
+    }
+}
+
 // z[o][p] = sum_k W[o][k] in[pos(p) + koff[k]]  (no bias, no activation)
-__device__ __forceinline__ void conv_z(const LdsStage &g, const float *in, const int *koff, const float *W, float *z) {
+__device__ __forceinline__ void conv_z(const LdsStage &g, const float *in, const int *koff, const float *W, float *z,
+                                       float *red) {
     constexpr int MT = 4;
     const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -45,7 +81,8 @@ __device__ __forceinline__ void conv_z(const LdsStage &g, const float *in, const
     constexpr int D = 16;
     float wa[D], wb[D];
     int last = -1;
-    for (int job = wave; job < RG * CT; job += NW) {
+    const KSplit sp = split_k(RG * CT, wave, Kt);
+    for (int job = sp.job0; job < RG * CT; job += sp.stride) {
         const int ct = job / RG, rg = job - ct * RG;
         f4 acc[MT];
         int base[MT];
@@ -61,37 +98,40 @@ __device__ __forceinline__ void conv_z(const LdsStage &g, const float *in, const
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 const int k = k0 + 4 * d + lg;
-                b[d] = w[k < Kt ? k : 0];
+                b[d] = w[k < sp.k1 ? k : 0];
             }
         };
         auto run = [&](const float (&b)[D], int k0) {
 #pragma unroll
             for (int d0 = 0; d0 < D; d0 += 4) {
-                if (k0 + 4 * d0 >= Kt) continue;
+                if (k0 + 4 * d0 >= sp.k1) continue;
                 float a[4][MT];
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    const int k = k0 + 4 * (d0 + d) + lg, ko = koff[k < Kt ? k : 0];
+                    const int k = k0 + 4 * (d0 + d) + lg, ko = koff[k < sp.k1 ? k : 0];
 #pragma unroll
-                    for (int i = 0; i < MT; ++i) a[d][i] = (k < Kt) ? in[base[i] + ko] : 0.0f;
+                    for (int i = 0; i < MT; ++i) a[d][i] = (k < sp.k1) ? in[base[i] + ko] : 0.0f;
                 }
 #pragma unroll
                 for (int d = 0; d < 4; ++d)
-                    if (k0 + 4 * (d0 + d) < Kt) step<MT>(a[d], (k0 + 4 * (d0 + d) + lg < Kt) ? b[d0 + d] : 0.0f, acc);
+                    if (k0 + 4 * (d0 + d) < sp.k1) step<MT>(a[d], (k0 + 4 * (d0 + d) + lg < sp.k1) ? b[d0 + d] : 0.0f, acc);
             }
         };
         // (a short kernel's weights stay in registers over the jobs of a column tile)
-        if (ct != last || Kt > 4 * D) load(wa, 0);
+        if (ct != last || sp.k1 - sp.k0 > 4 * D) load(wa, sp.k0);
         last = ct;
-        for (int k0 = 0; k0 < Kt; k0 += 8 * D) {
-            if (k0 + 4 * D < Kt) load(wb, k0 + 4 * D);
+        for (int k0 = sp.k0; k0 < sp.k1; k0 += 8 * D) {
+            if (k0 + 4 * D < sp.k1) load(wb, k0 + 4 * D);
             run(wa, k0);
-            if (k0 + 4 * D < Kt) {
-                if (k0 + 8 * D < Kt) load(wa, k0 + 8 * D);
+            if (k0 + 4 * D < sp.k1) {
+                if (k0 + 8 * D < sp.k1) load(wa, k0 + 8 * D);
                 run(wb, k0 + 4 * D);
             }
         }
-        if (o < g.O) {
+        if (sp.parts > 1) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) *(f4 *)(red + ((wave * MT + i) * 64 + lane) * 4) = acc[i];
+        } else if (o < g.O) {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -100,6 +140,10 @@ __device__ __forceinline__ void conv_z(const LdsStage &g, const float *in, const
                     if (p < P) z[o * P + p] = acc[i][r];
                 }
         }
+    }
+    if (sp.parts > 1) {
+        __syncthreads();
+        add_parts<MT>(red, RG * CT, sp.parts, RG, P, g.O, P, z);
     }
 }
 
@@ -137,13 +181,15 @@ __device__ __forceinline__ void conv_delta(const LdsStage &g, int fr, const floa
 }
 
 // e_in[c][q] = sum_{o,u,v} W[o][c][u][v] d[o][q - (u,v)], over the framed deltas
-__device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, const float *W, float *e_in) {
+__device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, const float *W, float *e_in,
+                                          float *red) {
     constexpr int MT = 4;
     const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int HW = g.H * g.W, KK = g.K * g.K, Kt = g.O * KK, RG = (HW + 16 * MT - 1) / (16 * MT), CT = (g.C + 15) / 16;
     const int PW = g.Wo + 2 * (g.K - 1), PP = (g.Ho + 2 * (g.K - 1)) * PW;
-    for (int job = wave; job < RG * CT; job += NW) {
+    const KSplit sp = split_k(RG * CT, wave, Kt);
+    for (int job = sp.job0; job < RG * CT; job += sp.stride) {
         const int ct = job / RG, rg = job - ct * RG;
         f4 acc[MT];
         int base[MT];
@@ -156,17 +202,17 @@ __device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, con
         const int c = 16 * ct + lr;
         const float *w = W + g.w_off + (c < g.C ? c : 0) * KK;
         constexpr int D = 16;
-        int o = 0, uv = lg;  // k = 4 steps + lg = o KK + uv
-        while (uv >= KK) { uv -= KK; ++o; }
+        int k = sp.k0 + lg, o = k / KK, uv = k - o * KK;  // k = o KK + uv
         float wa[D], wb[D];
         int ka[D], kb[D];
         auto load = [&](float (&b)[D], int (&ko)[D]) {
 #pragma unroll
             for (int s = 0; s < D; ++s) {
-                const bool in = o < g.O;
+                const bool in = k < sp.k1;
                 const int u = uv / g.K;
                 ko[s] = in ? o * PP + u * PW + uv - u * g.K : -1;
                 b[s] = w[in ? o * g.C * KK + KK - 1 - uv : 0];
+                k += 4;
                 uv += 4;
                 while (uv >= KK) { uv -= KK; ++o; }
             }
@@ -174,7 +220,7 @@ __device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, con
         auto run = [&](const float (&b)[D], const int (&ko)[D], int k0) {
 #pragma unroll
             for (int s0 = 0; s0 < D; s0 += 4) {
-                if (k0 + 4 * s0 >= Kt) continue;
+                if (k0 + 4 * s0 >= sp.k1) continue;
                 float a[4][MT];
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
@@ -182,19 +228,22 @@ __device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, con
                     for (int i = 0; i < MT; ++i) a[s][i] = (ko[s0 + s] >= 0) ? d[base[i] + ko[s0 + s]] : 0.0f;
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    if (k0 + 4 * (s0 + s) < Kt) step<MT>(a[s], ko[s0 + s] >= 0 ? b[s0 + s] : 0.0f, acc);
+                    if (k0 + 4 * (s0 + s) < sp.k1) step<MT>(a[s], ko[s0 + s] >= 0 ? b[s0 + s] : 0.0f, acc);
             }
         };
         load(wa, ka);
-        for (int k0 = 0; k0 < Kt; k0 += 8 * D) {
-            if (k0 + 4 * D < Kt) load(wb, kb);
+        for (int k0 = sp.k0; k0 < sp.k1; k0 += 8 * D) {
+            if (k0 + 4 * D < sp.k1) load(wb, kb);
             run(wa, ka, k0);
-            if (k0 + 4 * D < Kt) {
-                if (k0 + 8 * D < Kt) load(wa, ka);
+            if (k0 + 4 * D < sp.k1) {
+                if (k0 + 8 * D < sp.k1) load(wa, ka);
                 run(wb, kb, k0 + 4 * D);
             }
         }
-        if (c < g.C) {
+        if (sp.parts > 1) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) *(f4 *)(red + ((wave * MT + i) * 64 + lane) * 4) = acc[i];
+        } else if (c < g.C) {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -203,6 +252,10 @@ __device__ __forceinline__ void conv_back(const LdsStage &g, const float *d, con
                     if (q < HW) e_in[c * HW + q] = acc[i][r];
                 }
         }
+    }
+    if (sp.parts > 1) {
+        __syncthreads();
+        add_parts<MT>(red, RG * CT, sp.parts, RG, HW, g.C, HW, e_in);
     }
 }
 
@@ -374,7 +427,7 @@ __global__ void __launch_bounds__(NT, 2) worker_lds_kernel(LdsPlan pl, WorkArgs 
             if (g.fc) {
                 fc_forward(g, in, W, y);
             } else {
-                conv_z(g, in, (const int *)(lds + g.tab_off), W, z);
+                conv_z(g, in, (const int *)(lds + g.tab_off), W, z, red);
                 __syncthreads();
                 pool_act(g, z, W, y, (unsigned char *)(lds + g.arg_off));
             }
@@ -434,7 +487,7 @@ __global__ void __launch_bounds__(NT, 2) worker_lds_kernel(LdsPlan pl, WorkArgs 
                 conv_delta(g, fr, e, y, (const unsigned char *)(lds + g.arg_off), z);
                 __syncthreads();
                 if (l) {
-                    conv_back(g, z, W, ep);
+                    conv_back(g, z, W, ep, red);
                     __syncthreads();
                 }
                 conv_wgrad(g, fr, lin, (const int *)(lds + g.tab_off), z, red, push);

@@ -1,0 +1,67 @@
+"""The training worker that keeps its per-sample state in LDS (nets without a
+fused kernel), against the oracle, on MI355X: the layer lists of
+tests/test_gpu_batch.py, whose map counts, kernels, pooling windows and job
+counts (split and unsplit K, one and several tiles) are at the edges of its
+loops.  Per-sample SGD up to the first ambiguous max-pool tie, as the other
+sequential runs; concurrent workers at lr 0 see every sample once.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_1506_09067_amd import workloads as wl
+
+from ._compare import assert_close
+from .test_gpu_batch import NETS
+
+pytestmark = pytest.mark.gpu
+
+AMBIGUOUS = 2e-6
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1506_09067_amd import chaos
+    chaos.lib()
+    return torch, chaos
+
+
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_sequential_and_concurrent(env, name):
+    torch, chaos = env
+    hw, layers = NETS[name]
+    p = wl.init_params(layers, in_h=hw, in_w=hw)
+    n = 24
+    x = wl.images(n, 12, hw * hw)
+    net = chaos.Net(layers, p, in_h=hw, in_w=hw)
+    y = (wl.uniform_labels(n, 12) % min(net.n_out, 10)).astype(np.int32)
+    _, _, gaps = orc.train_sequential(layers, p, x, y, 1e-2, in_h=hw, in_w=hw, with_gaps=True)
+    amb = np.where(gaps < AMBIGUOUS)[0]
+    n_cut = int(amb[0]) if amb.size else n
+    assert n_cut >= 4
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    res = []
+    for mode, workers in ((chaos.SEQUENTIAL, 0), (chaos.HOGWILD_ATOMIC, 1), (chaos.HOGWILD_RACY, 1)):
+        net = chaos.Net(layers, p, in_h=hw, in_w=hw)
+        loss = torch.empty(n_cut, device="cuda")
+        net.train_epoch(xd[:n_cut], yd[:n_cut], 1e-2, mode=mode, workers=workers, loss=loss)
+        res.append((net.get_params(), loss))
+    torch.cuda.synchronize()
+    for w, l in res[1:]:
+        assert torch.equal(w, res[0][0]) and torch.equal(l, res[0][1])
+    w, l = res[0][0].cpu().numpy(), res[0][1].cpu().numpy()
+    p_ref, L_ref = orc.train_sequential(layers, p, x[:n_cut], y[:n_cut], 1e-2, in_h=hw, in_w=hw)
+    assert_close(l, L_ref, what=f"{name} losses")
+    assert_close(w, p_ref, what=f"{name} weights")
+    # fp32 storage of n_cut updates of 1e-2 of the weights' scale and below
+    assert_close(w - p, p_ref - p, tol=1e-3, what=f"{name} weight change")
+    claims = torch.zeros(n, dtype=torch.int32, device="cuda")
+    net = chaos.Net(layers, p, in_h=hw, in_w=hw)
+    net.set_claim_counter(claims)
+    net.train_epoch(xd, yd, 0.0, mode=chaos.HOGWILD_ATOMIC, workers=7)
+    net.set_claim_counter(None)
+    torch.cuda.synchronize()
+    assert torch.all(claims == 1) and torch.equal(net.get_params().cpu(), torch.from_numpy(p))
