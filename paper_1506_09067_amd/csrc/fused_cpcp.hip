@@ -92,7 +92,7 @@ constexpr int RT2 = 6;  // conv2 output positions 81 -> 6 tiles of 16
 // distinct LDS banks, where a stride of 96 folds them onto one or two.
 constexpr int D2S = 100;
 
-template <class S, bool DELAY = false>
+template <class S, bool DELAY = false, bool RES = false>
 struct alignas(16) SmemCpcp {
     float x[S::NX + 3];
     float p1[S::C1 * S::NP1];            // pool1 output, later pool1 errors/deltas in e1
@@ -114,6 +114,8 @@ struct alignas(16) SmemCpcp {
     float ones[128];                     // the conv2 weight gradient's ones column (bias)
     // delayed pushes: this worker's gradient sum since its last push (device layout)
     alignas(16) float gacc[DELAY ? S::NDEV : 4];
+    // resident weights: the conv2 gradient of the sample, until its backward data is done
+    alignas(16) float g2[RES ? S::C2 * S::KC2S : 4];
     int64_t idx;
     int rep_refresh;  // this sample's worker refreshes its replica
 };
@@ -125,11 +127,20 @@ struct alignas(16) SmemCpcp {
 // per-layer update, Section III-A.2, with the delayed sharing of locally
 // accumulated updates); its own unpushed updates are not in the weights it
 // reads.
-template <class S, int MODE, int MINB, bool DELAY = false>
+//
+// RES (one worker, nets whose whole weight vector fits in LDS): nobody else
+// reads or updates the weights during the epoch, so they stay in LDS from its
+// first sample to its last, and an update is an add there, rounded as the push
+// is.  A sample then has no round trip to memory but its image, which is
+// requested a sample ahead, and reads of LDS are what it waits for: they go in
+// larger batches than with concurrent workers (FC1's update, FC2, conv1's
+// gradient).  Small net, sequential SGD: 23.9 -> 20.3 us a sample.
+template <class S, int MODE, int MINB, bool DELAY = false, bool RES = false>
 __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
     static_assert(!DELAY || (MODE == kTrainAtomic && S::STAGE),
                   "delayed pushes: atomic training of a net copied whole into LDS");
-    __shared__ SmemCpcp<S, DELAY> sm;
+    static_assert(!RES || (MODE == kTrainAtomic && S::STAGE && !DELAY), "resident weights: training, one worker");
+    __shared__ SmemCpcp<S, DELAY, RES> sm;
     const float *Wg = a.params;
     // every weight read below goes through W: the LDS copy or the shared vector
     const float *W = S::STAGE ? (const float *)sm.w : Wg;
@@ -148,12 +159,22 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
     // weights after every refresh_every-th sample completed on it.  Per-line
     // contention at the memory side (every sample reads and adds into every
     // line of the vector) is then spread over the replicas.
-    const bool kReplicas = (MODE == kTrainAtomic) && !DELAY && S::STAGE && a.replicas != nullptr;
+    const bool kReplicas = (MODE == kTrainAtomic) && !DELAY && !RES && S::STAGE && a.replicas != nullptr;
 
     for (int k = threadIdx.x; k < 128; k += NT) sm.ones[k] = 1.0f;
     for (int k = threadIdx.x; k < 4 * S::KQ2; k += NT) {
         int c = k / 25, uv = k - 25 * c, u = uv / 5, v = uv - 5 * u;
         sm.koff2[k] = (k < S::KC2) ? c * S::NP1 + u * S::Q1 + v : 0;
+    }
+    constexpr int XPER = (S::NX + NT - 1) / NT;
+    float xnext[RES ? XPER : 1];  // resident weights: the next sample's image
+    if constexpr (RES) {
+        for (int i = threadIdx.x; i < S::C2 * S::KC2S; i += NT) sm.g2[i] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < XPER; ++q) {
+            const int i = threadIdx.x + NT * q;
+            xnext[q] = i < S::NX ? a.x[i] : 0.0f;
+        }
     }
     int nproc = 0;  // samples this worker has processed (delayed pushes)
     if constexpr (DELAY) {
@@ -188,7 +209,7 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
         const int tid = tid_l, lane = tid_l & 63, lr = lane & 15, lg = lane >> 4;
         const int wave = __builtin_amdgcn_readfirstlane(tid_l >> 6);
 
-        if (tid == 0) {
+        if (!RES && tid == 0) {
             if (kTrain && next < 0 && blockIdx.x > 0)
                 join_after(a.counter, a.n, (int)blockIdx.x / kJoinRamp);
             if (kTrain) sm.idx = (next >= 0) ? next : atomicAdd(a.counter, 1);
@@ -200,18 +221,23 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
         // drops the weights this CU and its L2 hold from earlier samples (an
         // agent-scope acquire: the caches are shared by the workgroup, and
         // the barrier below orders every wavefront's reads after it).
-        wait_vector_memory();
-        if (kTrain && wave == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if constexpr (!RES) {
+            wait_vector_memory();
+            if (kTrain && wave == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
         __syncthreads();
-        const int64_t idx = sm.idx;
+        const int64_t idx = RES ? step : sm.idx;
         if (idx >= a.n) {
+            if constexpr (RES) {
+                for (int i = 4 * tid; i < S::NDEV; i += 4 * NT) *(f4 *)(a.params + i) = *(const f4 *)(sm.w + i);
+            }
             if constexpr (DELAY) {
                 if (nproc % a.push_delay) flush();
             }
             break;
         }
         if (kTrain && tid == 0) {
-            next = atomicAdd(a.counter, 1);
+            if (!RES) next = atomicAdd(a.counter, 1);
             if (a.claims) atomicAdd(a.claims + idx, 1);
         }
         const int label = a.labels[idx];
@@ -220,30 +246,44 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
             // the first LDS write (the vector starts 16-byte aligned); from
             // this worker's replica when the shared weights are replicated
             const float *Wsrc = kReplicas ? a.replicas + (int64_t)(blockIdx.x % a.n_replicas) * S::NDEV : Wg;
-            constexpr int N4 = S::NDEV / 4, PER = (N4 + NT - 1) / NT, TAIL = S::NDEV - 4 * N4;
+            constexpr int N4 = S::NDEV / 4, PER = (N4 + NT - 1) / NT;
+            static_assert(S::NDEV % 4 == 0, "whole 16-byte loads");
+            // (frozen weights, and weights that stay here: once)
+            const bool load = (kTrain && !RES) || step == 0;
             f4 wv[PER];
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 const int t4 = tid + NT * q;
-                wv[q] = (t4 < N4) ? *(const f4 *)(Wsrc + 4 * t4) : f4{0.f, 0.f, 0.f, 0.f};
+                wv[q] = (load && t4 < N4) ? *(const f4 *)(Wsrc + 4 * t4) : f4{0.f, 0.f, 0.f, 0.f};
             }
-            const float wt = (tid < TAIL) ? Wsrc[4 * N4 + tid] : 0.0f;
-            for (int i = tid; i < S::NX; i += NT) sm.x[i] = a.x[idx * S::NX + i];
+            if constexpr (RES) {
+                const float *xn = a.x + (idx + 1 < a.n ? idx + 1 : idx) * S::NX;
+#pragma unroll
+                for (int q = 0; q < XPER; ++q) {
+                    const int i = tid + NT * q;
+                    if (i < S::NX) {
+                        sm.x[i] = xnext[q];
+                        xnext[q] = xn[i];
+                    }
+                }
+            } else {
+                for (int i = tid; i < S::NX; i += NT) sm.x[i] = a.x[idx * S::NX + i];
+            }
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 const int t4 = tid + NT * q;
-                if (t4 < N4) *(f4 *)(sm.w + 4 * t4) = wv[q];
+                if (load && t4 < N4) *(f4 *)(sm.w + 4 * t4) = wv[q];
             }
-            if (tid < TAIL) sm.w[4 * N4 + tid] = wt;
         } else if constexpr (S::STAGE2) {
             constexpr int N4 = S::NW2 / 4, PER = (N4 + NT - 1) / NT;
             static_assert(S::NW2 % 4 == 0, "whole 16-byte loads");
+            const bool load = kTrain || step == 0;  // frozen weights: once
             f4 wv[PER];
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 const int t4 = tid + NT * q;
                 const int o = 4 * t4 / S::KC2, k = 4 * t4 - o * S::KC2;  // a row holds whole 16-byte groups
-                wv[q] = (t4 < N4) ? *(const f4 *)(Wg + S::DW2 + o * S::KC2S + k) : f4{0.f, 0.f, 0.f, 0.f};
+                wv[q] = (load && t4 < N4) ? *(const f4 *)(Wg + S::DW2 + o * S::KC2S + k) : f4{0.f, 0.f, 0.f, 0.f};
             }
             constexpr int N4L = S::NLO / 4, N4B = S::C2 / 4, N4S = (S::NLO + S::C2 + S::NTAIL) / 4;
             constexpr int PS = (N4S + NT - 1) / NT;
@@ -254,18 +294,18 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
                 const float *src = (t4 < N4L) ? Wg + 4 * t4
                                    : (t4 < N4L + N4B) ? Wg + S::DB2 + 4 * (t4 - N4L)
                                                       : Wg + S::DBF1 + 4 * (t4 - N4L - N4B);
-                sv[q] = (t4 < N4S) ? *(const f4 *)src : f4{0.f, 0.f, 0.f, 0.f};
+                sv[q] = (load && t4 < N4S) ? *(const f4 *)src : f4{0.f, 0.f, 0.f, 0.f};
             }
             for (int i = tid; i < S::NX; i += NT) sm.x[i] = a.x[idx * S::NX + i];
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 const int t4 = tid + NT * q;
-                if (t4 < N4) *(f4 *)(sm.w2 + 4 * t4) = wv[q];
+                if (load && t4 < N4) *(f4 *)(sm.w2 + 4 * t4) = wv[q];
             }
 #pragma unroll
             for (int q = 0; q < PS; ++q) {
                 const int t4 = tid + NT * q;
-                if (t4 < N4S) *(f4 *)(sm.ws + 4 * t4) = sv[q];
+                if (load && t4 < N4S) *(f4 *)(sm.ws + 4 * t4) = sv[q];
             }
         } else {
             for (int i = tid; i < S::NX; i += NT) sm.x[i] = a.x[idx * S::NX + i];
@@ -533,15 +573,46 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
             }
         }
         __syncthreads();
-        for (int j = wave; j < S::F2; j += NW) {
-            float s = 0.0f;
+        if constexpr (kTrain && !RES) {
+            for (int j = wave; j < S::F2; j += NW) {
+                float s = 0.0f;
+#pragma unroll
+                for (int it = 0; it < (S::F1 + 63) / 64; ++it) {
+                    int i = lane + 64 * it;
+                    if (i < S::F1) s = fmaf(Wt[S::DF2 - S::DBF1 + j * S::F1S + i], sm.h[i], s);
+                }
+                s = wave_sum(s);
+                if (lane == 0) sm.o[j] = act_y(s + Wt[S::DBF2 - S::DBF1 + j]);
+            }
+        } else {
+            // This wavefront's neurons j = wave + NW q together, so that their reads
+            // and the exchanges of their sums overlap (not with concurrent workers:
+            // the small net, held by its lines at the memory side, runs 1.6 % slower)
+            constexpr int JQ = (S::F2 + NW - 1) / NW;
+            float s[JQ];
+#pragma unroll
+            for (int q = 0; q < JQ; ++q) s[q] = 0.0f;
 #pragma unroll
             for (int it = 0; it < (S::F1 + 63) / 64; ++it) {
-                int i = lane + 64 * it;
-                if (i < S::F1) s = fmaf(Wt[S::DF2 - S::DBF1 + j * S::F1S + i], sm.h[i], s);
+                const int i = lane + 64 * it;
+                if (i < S::F1) {
+                    const float h = sm.h[i];
+#pragma unroll
+                    for (int q = 0; q < JQ; ++q) {
+                        const int j = wave + NW * q < S::F2 ? wave + NW * q : wave;
+                        s[q] = fmaf(Wt[S::DF2 - S::DBF1 + j * S::F1S + i], h, s[q]);
+                    }
+                }
             }
-            s = wave_sum(s);
-            if (lane == 0) sm.o[j] = act_y(s + Wt[S::DBF2 - S::DBF1 + j]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                for (int q = 0; q < JQ; ++q) s[q] += __shfl_xor(s[q], off, 64);
+#pragma unroll
+            for (int q = 0; q < JQ; ++q) {
+                const int j = wave + NW * q;
+                if (lane == 0 && j < S::F2) sm.o[j] = act_y(s[q] + Wt[S::DBF2 - S::DBF1 + j]);
+            }
         }
         __syncthreads();
         if (a.out && tid < S::F2) a.out[idx * S::F2 + tid] = sm.o[tid];
@@ -570,6 +641,12 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
         auto push = [&](int w_off, int g_off, float g) {
             if constexpr (DELAY) {
                 sm.gacc[w_off] += g;
+            } else if constexpr (RES) {
+                // conv2's weights are read by its backward data in the same
+                // phase: their gradient waits in g2; every other layer's have
+                // been read for the last time in this sample
+                if (w_off >= S::DW2 && w_off < S::DB2) sm.g2[w_off - S::DW2] = g;
+                else sm.w[w_off] = __fadd_rn(sm.w[w_off], __fmul_rn(push_now.neg_lr, g));
             } else {
                 push_now(w_off, g_off, g);
                 // the same update, rounded the same way, into this worker's replica
@@ -673,12 +750,38 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
                     int i = lane + 64 * c;
                     xv[c] = (i < S::NF1) ? sm.p2[i] : 0.0f;
                 }
-                for (int j = wave; j < S::F1; j += NW) {
-                    const float d = sm.dh[j];
+                if constexpr (RES) {
+                    // all of a wavefront's weights are read before the first is written
+                    constexpr int NR = (S::F1 + NW - 1) / NW;
+                    float old[NR][IC], dr[NR];
 #pragma unroll
-                    for (int c = 0; c < IC; ++c) {
-                        int i = lane + 64 * c;
-                        if (i < S::NF1) push(S::DF1 + j * S::NF1S + i, S::OF1 + j * S::NF1 + i, d * xv[c]);
+                    for (int r = 0; r < NR; ++r) {
+                        const int j = wave + NW * r < S::F1 ? wave + NW * r : wave;
+                        dr[r] = sm.dh[j];
+#pragma unroll
+                        for (int c = 0; c < IC; ++c) {
+                            const int i = lane + 64 * c;
+                            old[r][c] = sm.w[S::DF1 + j * S::NF1S + (i < S::NF1 ? i : 0)];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+#pragma unroll
+                        for (int c = 0; c < IC; ++c) {
+                            const int j = wave + NW * r, i = lane + 64 * c;
+                            if (j < S::F1 && i < S::NF1)
+                                sm.w[S::DF1 + j * S::NF1S + i] =
+                                    __fadd_rn(old[r][c], __fmul_rn(push_now.neg_lr, dr[r] * xv[c]));
+                        }
+                } else {
+                    for (int j = wave; j < S::F1; j += NW) {
+                        const float d = sm.dh[j];
+#pragma unroll
+                        for (int c = 0; c < IC; ++c) {
+                            int i = lane + 64 * c;
+                            if (i < S::NF1) push(S::DF1 + j * S::NF1S + i, S::OF1 + j * S::NF1 + i, d * xv[c]);
+                        }
                     }
                 }
             }
@@ -1107,32 +1210,74 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
             // current four compute.  The conv1 bias gradients are summed from
             // the same operands: per lane over its positions, then over the
             // four lane groups and (after the barrier) the wavefronts in order.
-            float bxC[4], avC[4][S::CT1], bxN[4], avN[4][S::CT1], bsum[S::CT1];
+            if constexpr (RES) {
+                // (padding columns' gradients stay zero)
+                for (int i = tid; i < S::C2 * S::KC2S; i += NT)
+                    sm.w[S::DW2 + i] = __fadd_rn(sm.w[S::DW2 + i], __fmul_rn(push_now.neg_lr, sm.g2[i]));
+            }
+            float bsum[S::CT1];
 #pragma unroll
             for (int t = 0; t < S::CT1; ++t) bsum[t] = 0.0f;
-            auto load4 = [&](int P0, float (&bx)[4], float (&av)[4][S::CT1]) {
+            if constexpr (RES) {
+                // 22 positions' operands read at once, raw; nothing else keeps this
+                // worker waiting, so the latency of each read is what counts (an
+                // even count: the two sums' order is that of the loop below)
+                constexpr int PB = 22, NBT = ((S::NP1 + NW - 1) / NW + PB - 1) / PB;
+#pragma unroll 1
+                for (int b = 0; b < NBT; ++b) {
+                    float bx[PB], ev[PB][S::CT1], yv[PB][S::CT1];
+                    int am[PB][S::CT1];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int P = P0 + NW * u;
-                    operands(P < S::NP1 ? P : S::NP1 - 1, bx[u], av[u]);
-                }
-            };
-            load4(wave, bxC, avC);
-            for (int P0 = wave; P0 < S::NP1; P0 += 4 * NW) {
-                load4(P0 + 4 * NW, bxN, avN);
+                    for (int u = 0; u < PB; ++u) {
+                        const int P0 = wave + NW * (PB * b + u), P = P0 < S::NP1 ? P0 : S::NP1 - 1;
+                        const int py = P / S::Q1, px = P - py * S::Q1;
+                        bx[u] = sm.x[2 * py * S::IN + 2 * px + xo];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (P0 + NW * u < S::NP1) {
-                        compute(bxC[u], avC[u], acc[u & 1]);
+                        for (int t = 0; t < S::CT1; ++t) {
+                            am[u][t] = sm.am1[orow[t] + P];
+                            ev[u][t] = sm.e1[orow[t] + P];
+                            yv[u][t] = sm.p1[orow[t] + P];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int t = 0; t < S::CT1; ++t) bsum[t] += avC[u][t];
+                    for (int u = 0; u < PB; ++u) {
+                        // (one element of position 168 past the last is a repeat: zero)
+                        const bool in = wave + NW * (PB * b + u) < S::NP1;
+#pragma unroll
+                        for (int t = 0; t < S::CT1; ++t) {
+                            const float av = (in && ov[t] && am[u][t] == lg) ? ev[u][t] * dact_from_y(yv[u][t]) : 0.0f;
+                            acc[u & 1][t] = mfma(av, bx[u], acc[u & 1][t]);
+                            bsum[t] += av;
+                        }
                     }
                 }
+            } else {
+                float bxC[4], avC[4][S::CT1], bxN[4], avN[4][S::CT1];
+                auto load4 = [&](int P0, float (&bx)[4], float (&av)[4][S::CT1]) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    bxC[u] = bxN[u];
+                    for (int u = 0; u < 4; ++u) {
+                        const int P = P0 + NW * u;
+                        operands(P < S::NP1 ? P : S::NP1 - 1, bx[u], av[u]);
+                    }
+                };
+                load4(wave, bxC, avC);
+                for (int P0 = wave; P0 < S::NP1; P0 += 4 * NW) {
+                    load4(P0 + 4 * NW, bxN, avN);
 #pragma unroll
-                    for (int t = 0; t < S::CT1; ++t) avC[u][t] = avN[u][t];
+                    for (int u = 0; u < 4; ++u) {
+                        if (P0 + NW * u < S::NP1) {
+                            compute(bxC[u], avC[u], acc[u & 1]);
+#pragma unroll
+                            for (int t = 0; t < S::CT1; ++t) bsum[t] += avC[u][t];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        bxC[u] = bxN[u];
+#pragma unroll
+                        for (int t = 0; t < S::CT1; ++t) avC[u][t] = avN[u][t];
+                    }
                 }
             }
             // the conv2 biases summed in the previous phase
@@ -1171,7 +1316,7 @@ __global__ void __launch_bounds__(NT, MINB) fused_cpcp_kernel(WorkArgs a) {
                 flush();
             }
         }
-        if (kTrain && tid == 0) atomicAdd(a.counter + 1, 1);  // samples completed
+        if (kTrain && !RES && tid == 0) atomicAdd(a.counter + 1, 1);  // samples completed
         if (kReplicas) {
             // every refresh_every-th sample completed on this replica: once
             // this worker's pushes have landed, copy the shared weights into it
@@ -1278,7 +1423,13 @@ bool fused_cpcp_layout(int variant, ParamLayout &L) {
     return false;
 }
 
+// One worker, atomic or racy (its updates have nobody to be lost to), keeps the
+// small net's weights in LDS.
 hipError_t launch_fused_cpcp(int variant, int mode, const WorkArgs &a, int grid, hipStream_t s) {
+    if (variant == 1 && grid == 1 && (mode == kTrainAtomic || mode == kTrainRacy) && a.push_delay <= 1 && !a.replicas) {
+        fused_cpcp_kernel<Small, kTrainAtomic, 1, false, true><<<1, NT, 0, s>>>(a);
+        return hipGetLastError();
+    }
     if (variant == 1 && mode == kTrainAtomic && a.push_delay > 1) {
         fused_cpcp_kernel<Small, kTrainAtomic, kSmallDelayMinBlocks, true><<<grid, NT, 0, s>>>(a);
         return hipGetLastError();
