@@ -1241,6 +1241,172 @@ __global__ void __launch_bounds__(256 * WR, WR == 1 ? 2 : 1) conv_wgrad_kernel(W
         }
 }
 
+// ---- weight gradient of the first layer --------------------------------------
+// G[o][k] = sum over samples and positions of d * x under the kernel, few columns
+// (the kernel's pixels) and many positions.  In the split kernel above the work is
+// nearly all staging: each pixel split once per kernel position, three planes of
+// every zero between the maxima.  Here x and the deltas (dense, one sample) lie in
+// LDS as fp32, the wavefronts take every fourth step of four positions on the fp32
+// 16x16x4 instruction, and a sample's sums are added to the chunk's.  8,192 samples
+// of the large net: 424 us with the split kernel, 190 us here (two workgroups to a
+// CU, held by the latency of a sample's loads).
+struct FirstWgradArgs {
+    DeltaArgs d;
+    const float *x;
+    float *part, *each;
+    int64_t n, spc;            // samples, samples per chunk
+    int64_t rowsize, each_stride;
+    int HW, W, K, KK, O, P, Wo, nout, CQ, RTT;
+    int d_off, k_off;          // LDS offsets in floats
+    int accumulate, cw_off, cb_off;
+    FastDiv fO, fWp, fWo, fK;
+};
+
+template <int RT, int CT>
+__global__ void __launch_bounds__(NT_, 2) first_wgrad_kernel(FirstWgradArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *xs = lds, *ds = lds + a.d_off;
+    int *koff = (int *)(lds + a.k_off);
+    for (int k = tid; k < 16 * CT; k += NT_) {
+        const int u = fdiv(k, a.fK);
+        koff[k] = k < a.KK ? u * a.W + k - u * a.K : 0;
+    }
+    f4 acc[RT][CT];
+    float bias[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        bias[i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int64_t s0 = blockIdx.x * a.spc, s1 = (s0 + a.spc < a.n) ? s0 + a.spc : a.n;
+    for (int64_t s = s0; s < s1; ++s) {
+        __syncthreads();  // the previous sample's operands have been read
+        const float *xg = a.x + s * a.HW;
+        for (int i = tid; i < a.HW; i += NT_) xs[i] = xg[i];
+        // deltas [map][position]: without pooling every element, else zeros but at
+        // the recorded maxima
+        const float *eg = a.d.e + s * a.nout, *yg = a.d.y + s * a.nout;
+        const uint8_t *ag = a.d.arg + s * a.nout;
+        if (a.d.p > 1) {
+            for (int i = tid; i < a.O * a.P / 4; i += NT_) ((f4 *)ds)[i] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int i = a.O * a.P / 4 * 4 + tid; i < a.O * a.P; i += NT_) ds[i] = 0.0f;
+            __syncthreads();
+        }
+        constexpr int U = 4;
+        for (int i0 = tid; i0 < a.nout; i0 += U * NT_) {
+            float ev[U], yv[U];
+            int av[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_ < a.nout ? i0 + q * NT_ : i0;
+                ev[q] = eg[i];
+                yv[q] = yg[i];
+                av[q] = a.d.p > 1 ? ag[i] : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q * NT_, pp = fdiv(i, a.fO), o = i - pp * a.O;
+                const int py = fdiv(pp, a.fWp), px = pp - py * a.d.Wp, u = fdiv(av[q], a.d.fp);
+                const int pos = (py * a.d.p + u) * a.Wo + px * a.d.p + av[q] - u * a.d.p;
+                if (i < a.nout) ds[o * a.P + pos] = ev[q] * dact_from_y(yv[q]);
+            }
+        }
+        __syncthreads();
+        f4 t[RT][CT];
+        float tb[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            tb[i] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < CT; ++j) t[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        int ko[CT];
+        const float *dr[RT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) ko[j] = koff[16 * j + lr];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) dr[i] = ds + (16 * i + lr < a.O ? 16 * i + lr : 0) * a.P;
+        constexpr int B = 4;  // steps whose operands are read together
+        for (int p0 = 4 * wave; p0 < a.P; p0 += 16 * B) {
+            float av[B][RT], bv[B][CT];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int p = p0 + 16 * b + lg, pc = p < a.P ? p : 0, y = fdiv(pc, a.fWo), base = y * a.W + pc - y * a.Wo;
+#pragma unroll
+                for (int i = 0; i < RT; ++i) av[b][i] = dr[i][pc];
+#pragma unroll
+                for (int j = 0; j < CT; ++j) bv[b][j] = xs[base + ko[j]];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const bool in = p0 + 16 * b + lg < a.P;  // past the last position: nothing
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    const float v = in ? av[b][i] : 0.0f;
+                    tb[i] += v;
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) t[i][j] = mfma(v, in ? bv[b][j] : 0.0f, t[i][j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            bias[i] += tb[i];
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] += t[i][j];
+        }
+    }
+    // the wavefronts' sums in order (through the deltas' space), then out
+    __syncthreads();
+    float *red = ds, *redb = ds + 4 * RT * CT * 256;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j) *(f4 *)(red + (((wave * RT + i) * CT + j) * 64 + lane) * 4) = acc[i][j];
+        float b = bias[i] + __shfl_xor(bias[i], 16, 64);
+        b += __shfl_xor(b, 32, 64);
+        if (lg == 0) redb[(wave * RT + i) * 16 + lr] = b;
+    }
+    __syncthreads();
+    float *row = a.part + blockIdx.x * a.rowsize;
+    float *g = a.each ? a.each + blockIdx.x * a.each_stride : nullptr;
+    for (int e = tid; e < RT * CT * 64; e += NT_) {
+        const int l = e & 63, ij = e >> 6, i = ij / CT, j = ij - i * CT;
+        f4 v = *(const f4 *)(red + e * 4);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += *(const f4 *)(red + (w * RT * CT * 64 + e) * 4);
+        if (g) {
+            const int k = 16 * j + (l & 15);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int o = 16 * i + 4 * (l >> 4) + r;
+                if (o < a.O && k < a.KK) g[a.cw_off + o * a.KK + k] = v[r];
+            }
+        } else if ((l & 15) != 4 * (a.CQ & 3) || j != a.CQ >> 2) {
+            float *dst = row + ((j * a.RTT + i) * 64 + l) * 4;
+            if (a.accumulate) v += *(const f4 *)dst;
+            *(f4 *)dst = v;
+        }
+    }
+    for (int o = tid; o < a.O; o += NT_) {
+        float v = redb[(o >> 4) * 16 + (o & 15)];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += redb[(w * RT + (o >> 4)) * 16 + (o & 15)];
+        if (g) {
+            g[a.cb_off + o] = v;
+        } else {
+            // the column after the kernel's quads
+            const int l = ((o & 15) >> 2) * 16 + 4 * (a.CQ & 3);
+            float *dst = row + (((a.CQ >> 2) * a.RTT + (o >> 4)) * 64 + l) * 4 + (o & 3);
+            *dst = a.accumulate ? *dst + v : v;
+        }
+    }
+}
+
 // Partial rows of every layer summed in order (compensated), into the
 // canonical gradient.
 struct ReduceDesc {
@@ -1522,6 +1688,7 @@ struct WgradCfg {
     int rtm, ctm, wr;
     int S, NB, RB, NCQ, C8s, sts, o8s, osts, tgs, ctw, kw, ncg, gz, tab, in_off, d_off, cst, npmax;
     int im2col, C, T, CQ, RTT;
+    int first;  // the first layer's own kernel
     int64_t bytes, units, upc, chunks, rowsize;
 };
 bool wgrad_lds(const Stage &g, WgradCfg &c) {
@@ -1543,6 +1710,28 @@ bool pick_wgrad(const Stage &g, bool first, int64_t n, bool each, WgradCfg &c) {
     c.T = first ? 1 : g.T;
     c.CQ = (int)cdiv(c.C, 4);
     c.RTT = (int)cdiv(g.O, 16);
+    if (first) {
+        // up to 32 maps and 32 kernel pixels, one sample's deltas in half the LDS
+        const int ct = (int)cdiv(c.C, 16);
+        const int64_t d_off = cdiv((int64_t)g.H * g.W, 4) * 4;
+        const int64_t d = std::max<int64_t>(cdiv((int64_t)g.O * g.P, 4) * 4, 4 * c.RTT * ct * 256 + 4 * c.RTT * 16);
+        c.bytes = (d_off + d + 16 * ct) * 4;
+        if (c.RTT <= 2 && ct <= 2 && c.bytes <= kLds / 2) {
+            c.first = 1;
+            c.in_off = (int)d_off;
+            c.tab = (int)(d_off + d);
+            c.S = c.NB = c.ncg = c.tgs = c.gz = c.kw = 1;
+            c.ctw = 1;
+            c.NCQ = c.CQ;
+            c.units = n;
+            const int64_t per_cu = std::min<int64_t>(4, kLds / c.bytes);
+            c.chunks = each ? n : std::min(n, kCus * per_cu);
+            c.upc = cdiv(n, c.chunks);
+            c.chunks = cdiv(n, c.upc);
+            c.rowsize = 4 * c.RTT * 256;  // four column tiles, of which the kernel's and the bias's are used
+            return true;
+        }
+    }
     c.rtm = c.RTT <= 1 ? 1 : c.RTT <= 2 ? 2 : c.RTT <= 8 ? 4 : 5;
     c.wr = c.RTT <= 4 ? 1 : 2;
     c.ctm = c.rtm == 5 ? 6 : 8;
@@ -1665,6 +1854,46 @@ WgradIndex wgrad_index_of(const Stage &g, const WgradCfg &c) {
     return x;
 }
 
+hipError_t launch_first_wgrad(const Stage &g, const WgradCfg &c, const float *x, const float *e, const float *y,
+                              const uint8_t *arg, int64_t n, float *part, bool accumulate, float *each,
+                              int64_t each_stride, hipStream_t s) {
+    FirstWgradArgs a{};
+    a.d = delta_args(g, e, y, arg);
+    a.x = x;
+    a.part = part;
+    a.each = each;
+    a.n = n;
+    a.spc = c.upc;
+    a.rowsize = c.rowsize;
+    a.each_stride = each_stride;
+    a.HW = g.H * g.W;
+    a.W = g.W;
+    a.K = g.K;
+    a.KK = g.K * g.K;
+    a.O = g.O;
+    a.P = g.P;
+    a.Wo = g.Wo;
+    a.nout = g.nout;
+    a.CQ = c.CQ;
+    a.RTT = c.RTT;
+    a.d_off = c.in_off;
+    a.k_off = c.tab;
+    a.accumulate = accumulate;
+    a.cw_off = g.cw_off;
+    a.cb_off = g.cb_off;
+    a.fO = fast_div(g.O);
+    a.fWp = fast_div(g.Wp);
+    a.fWo = fast_div(g.Wo);
+    a.fK = fast_div(g.K);
+    const unsigned grid = (unsigned)cdiv(n, c.upc);
+    const int ct = (int)cdiv(a.KK, 16);
+    if (c.RTT == 1 && ct == 1) first_wgrad_kernel<1, 1><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    else if (c.RTT == 1) first_wgrad_kernel<1, 2><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    else if (ct == 1) first_wgrad_kernel<2, 1><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    else first_wgrad_kernel<2, 2><<<grid, NT_, (size_t)c.bytes, s>>>(a);
+    return hipGetLastError();
+}
+
 template <int RTM, int CTM, int WR>
 hipError_t run_wgrad(const WgradArgs &a, const WgradIndex &x, dim3 grid, int64_t bytes, hipStream_t s) {
     conv_wgrad_kernel<RTM, CTM, WR><<<grid, 256 * WR, (size_t)bytes, s>>>(a, x);
@@ -1674,6 +1903,7 @@ hipError_t run_wgrad(const WgradArgs &a, const WgradIndex &x, dim3 grid, int64_t
 hipError_t launch_wgrad(const Stage &g, const WgradCfg &c, const float *in, const float *e, const float *y,
                         const uint8_t *arg, int64_t n, float *part, bool accumulate, float *each, int64_t each_stride,
                         hipStream_t s) {
+    if (c.first) return launch_first_wgrad(g, c, in, e, y, arg, n, part, accumulate, each, each_stride, s);
     WgradArgs a{};
     a.d = delta_args(g, e, y, arg);
     a.in = in;
