@@ -249,26 +249,30 @@ int64_t pass_samples(const chaos_net *net, int64_t n, int64_t bytes, bool grads)
 }
 
 // Which calls go to the batched engine.  A net's own kernel runs a sample from
-// the image to its gradient in one workgroup, so up to one sample per compute
-// unit it takes one sample's time; the engine's launches (one per layer and
-// direction) take longer than that, but spread a few samples over the whole GPU
-// and keep the matrix cores busy with many.  Measured, us (own kernel / engine):
-//   evaluate  large 256: 84 / 110, 300: 163 / 125, 10000: 3166 / 1720;
-//             medium 300: 63 / 71, 10000: 1143 / 584; small 10000: 199 / 252
-//   gradient  medium 16: 158 / 172, 1024: 537 / 338; small 16: 43 / 139,
-//             16384: 1063 / 1597
+// the image to its gradient in one workgroup: up to one sample per compute unit
+// takes one sample's time, and the small net, whose layers fill a few tiles, keeps
+// its values in LDS from end to end.  The engine's launches (one per layer and
+// direction) take longer than a sample of the smaller nets, but spread a few
+// samples of the large ones over the whole GPU and keep the matrix cores busy with
+// many.  Measured, us (own kernel / engine):
+//   evaluate  large 1: 82 / 65, 128: 83 / 81, 256: 87 / 95, 512: 129 / 125;
+//             Table I large 1: 153 / 83, 256: 157 / 150;
+//             medium 256: 34 / 57, 400: 61 / 66, 600: 88 / 72;
+//             small 4000: 79 / 98, 10000: 191 / 190, 30000: 556 / 514
+//   gradient  medium 128: 164 / 200, 256: 238 / 216, 700: 431 / 291;
+//             small 256: 108 / 148, 1000: 216 / 214, 16384: 1043 / 1193
 // (the large nets' own kernels have no frozen-weight gradient).  Per-sample
 // gradients always take the engine, so that a max-pool near-tie is resolved as
 // in the sums they are compared with.
 bool batched_evaluate(const chaos_net *net, int64_t n) {
     if (!net->plan.ok) return false;
-    if (net->fused || net->t1) return n > net->cus;
-    if (net->cpcp) return net->cpcp == 2 && n >= 1024;
+    if (net->fused) return n <= net->cus * 3 / 4 || n > net->cus;
+    if (net->cpcp) return n >= (net->cpcp == 2 ? 2 * net->cus : 64 * net->cus);
     return true;
 }
 bool batched_gradient(const chaos_net *net, int64_t n, const float *sum, const float *each) {
     if (!net->plan.ok || !(sum || each)) return false;
-    if (net->cpcp && !each) return net->cpcp == 2 && n >= 512;
+    if (net->cpcp && !each) return net->cpcp == 2 && n >= net->cus;
     return true;
 }
 

@@ -190,14 +190,18 @@ __device__ __forceinline__ float dact_from_y(float y) {
 // maximum of z: the window is compared on z and f is evaluated once.  (Where
 // f would round two different z to the same fp32 value, the larger z wins,
 // which is the maximum of the exact f.)
-__device__ __forceinline__ void pool4(f4 acc, float bias, float &ymax, int &arg) {
-    float zmax = acc[0] + bias;
+__device__ __forceinline__ void pool4_z(f4 acc, float bias, float &zmax, int &arg) {
+    zmax = acc[0] + bias;
     arg = 0;
 #pragma unroll
     for (int r = 1; r < 4; ++r) {
         float z = acc[r] + bias;
         if (z > zmax) { zmax = z; arg = r; }
     }
+}
+__device__ __forceinline__ void pool4(f4 acc, float bias, float &ymax, int &arg) {
+    float zmax;
+    pool4_z(acc, bias, zmax, arg);
     ymax = act_y(zmax);
 }
 
