@@ -15,7 +15,8 @@
 //   weight gradient  rows = maps, columns = (map, kernel), K = output positions
 // Every reduction has a fixed order, so one worker is sequential SGD bit for bit.
 // A net of conv 16, 32, 48 and two FC layers on 32x32 inputs (68,826 weights):
-// 600 us a sample and worker before, see the figures at launch_worker_lds.
+// 1,495 -> 130 us a sample of one worker, an epoch of 1,044 samples by 256
+// workers 7.73 -> 0.82 ms against the worker with its state in device memory.
 #include "batch.h"
 #include "chaos_internal.h"
 #include "device_common.h"

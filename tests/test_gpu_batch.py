@@ -124,13 +124,13 @@ def test_batched_engine_with_pixels_that_are_not_finite(env, value):
     ref = torch.empty(300, 10, device="cuda")
     net.evaluate(xd, y, out=ref)
     xd[7, 400] = value
-    out, own = torch.empty_like(ref), torch.empty(1, 10, device="cuda")
+    out, own = torch.empty_like(ref), torch.empty(256, 10, device="cuda")
     net.evaluate(xd, y, out=out)
-    net.evaluate(xd[7:8].contiguous(), y[:1], out=own)
+    net.evaluate(xd[:256].contiguous(), y[:256], out=own)  # one sample a workgroup: the per-sample kernel
     torch.cuda.synchronize()
     keep = [i for i in range(300) if i != 7]
     assert torch.equal(out[keep], ref[keep])
     if value == float("inf"):
-        assert_close(out[7].cpu().numpy(), own[0].cpu().double().numpy(), what="saturated sample")
+        assert_close(out[7].cpu().numpy(), own[7].cpu().double().numpy(), what="saturated sample")
     else:
-        assert torch.isnan(out[7]).all() == torch.isnan(own[0]).all()
+        assert torch.isnan(out[7]).all() == torch.isnan(own[7]).all()
