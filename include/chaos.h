@@ -15,9 +15,10 @@
  *    work is enqueued on `stream` and is asynchronous: the caller
  *    synchronises (hipStreamSynchronize / torch.cuda.synchronize) before it
  *    reads results.  stream = NULL means the null stream.
- *  - One call at a time per chaos_net, its device work included (calls of one
- *    net that overlap on different streams race on the net's workspace);
- *    different nets are independent.
+ *  - One call at a time per chaos_net; different nets are independent.  Calls
+ *    that share the net's workspace (evaluation, forward/backward) wait on the
+ *    device for one another when they are on different streams; replays of a
+ *    graph that captured such a call are ordered by the program.
  *  - Images are fp32, row-major [n][in_h * in_w]; labels int32 in
  *    [0, n_classes) where n_classes is the output size of the last layer.
  *    Labels live in device memory and are not range-checked: a label

@@ -55,6 +55,8 @@ struct chaos_net {
     int64_t act_bytes = 0;
     void *grad_act = nullptr;     // and those of a gradient, allocated on first use
     int64_t grad_bytes = 0;
+    std::mutex engine_mutex;      // one call at a time enqueues on the engine's workspace,
+    hipEvent_t engine_done = nullptr;  // and waits for the last one's work
 };
 
 // Partial-sum rows of chaos_forward_backward_noalloc: a fixed array on every
@@ -255,9 +257,9 @@ int64_t pass_samples(const chaos_net *net, int64_t n, int64_t bytes, bool grads)
 // direction) take longer than a sample of the smaller nets, but spread a few
 // samples of the large ones over the whole GPU and keep the matrix cores busy with
 // many.  Measured, us (own kernel / engine):
-//   evaluate  large 1: 82 / 65, 128: 83 / 81, 256: 87 / 95, 512: 129 / 125;
-//             Table I large 1: 153 / 83, 256: 157 / 150;
-//             medium 256: 34 / 57, 400: 61 / 66, 600: 88 / 72;
+//   evaluate  large 1: 82 / 70, 64: 82 / 78, 128: 83 / 86, 256: 87 / 100, 512: 129 / 130;
+//             Table I large 1: 153 / 88, 256: 157 / 155;
+//             medium 256: 34 / 62, 400: 61 / 71, 600: 88 / 77;
 //             small 4000: 79 / 98, 10000: 191 / 190, 30000: 556 / 514
 //   gradient  medium 128: 164 / 200, 256: 238 / 216, 700: 431 / 291;
 //             small 256: 108 / 148, 1000: 216 / 214, 16384: 1043 / 1193
@@ -266,8 +268,8 @@ int64_t pass_samples(const chaos_net *net, int64_t n, int64_t bytes, bool grads)
 // in the sums they are compared with.
 bool batched_evaluate(const chaos_net *net, int64_t n) {
     if (!net->plan.ok) return false;
-    if (net->fused) return n <= net->cus * 3 / 4 || n > net->cus;
-    if (net->cpcp) return n >= (net->cpcp == 2 ? 2 * net->cus : 64 * net->cus);
+    if (net->fused) return n <= net->cus * 3 / 8 || n > net->cus;
+    if (net->cpcp) return n > (net->cpcp == 2 ? 2 * net->cus : 64 * net->cus);
     return true;
 }
 bool batched_gradient(const chaos_net *net, int64_t n, const float *sum, const float *each) {
@@ -282,8 +284,40 @@ bool batched_losses(const chaos_net *net, const float *sum, const float *each) {
     return net->plan.ok && !net->fused && !net->t1 && !net->cpcp && !sum && !each;
 }
 
-hipError_t batch_gradient(chaos_net *net, const chaos::BatchWork &w, const float *x, const int32_t *labels, int64_t n,
-                          float *out, float *loss, float *grad_sum, float *grad_each, hipStream_t s) {
+// A call's turn on the engine's workspace.  The kernels of two calls may not
+// meet there, but calls on different streams (or threads) may: each waits on the
+// device for the one before.  Recording the event takes 5 us of a call (large net,
+// one sample: 64.6 -> 69.6), the wait on one stream nothing.  A captured call
+// does neither: a graph's replays are ordered by the program.
+class EngineTurn {
+public:
+    EngineTurn(chaos_net *net, hipStream_t s) : lock_(net->engine_mutex), net_(net), stream_(s) {}
+    hipError_t begin() {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(stream_, &st);
+        if (e != hipSuccess) return e;
+        captured_ = st != hipStreamCaptureStatusNone;
+        return captured_ ? hipSuccess : hipStreamWaitEvent(stream_, net_->engine_done, 0);
+    }
+    hipError_t end() { return captured_ ? hipSuccess : hipEventRecord(net_->engine_done, stream_); }
+
+private:
+    std::lock_guard<std::mutex> lock_;
+    chaos_net *net_;
+    hipStream_t stream_;
+    bool captured_ = false;
+};
+
+// one call's launches, in its turn
+hipError_t run_engine(EngineTurn &turn, const chaos_net *net, const chaos::BatchWork &w, const chaos::BatchCall &c,
+                      hipStream_t s) {
+    hipError_t e = chaos::launch_batch(net->plan, w, c, s);
+    const hipError_t done = turn.end();
+    return e == hipSuccess ? done : e;
+}
+
+hipError_t batch_gradient(EngineTurn &turn, chaos_net *net, const chaos::BatchWork &w, const float *x,
+                          const int32_t *labels, int64_t n, float *out, float *loss, float *grad_sum, float *grad_each, hipStream_t s) {
     chaos::BatchCall c{};
     c.params = net->params;
     c.x = x;
@@ -294,7 +328,7 @@ hipError_t batch_gradient(chaos_net *net, const chaos::BatchWork &w, const float
     c.grad_sum = grad_sum;
     c.grad_each = grad_each;
     c.n_params = net->n_params;
-    return chaos::launch_batch(net->plan, w, c, s);
+    return run_engine(turn, net, w, c, s);
 }
 
 hipError_t launch(chaos_net *net, int mode, const chaos::WorkArgs &a, int grid, hipStream_t s) {
@@ -390,9 +424,14 @@ int chaos_create_net(int32_t in_h, int32_t in_w, const chaos_layer *layers, int3
         // at least four samples of a gradient
         if (net->plan.ok && 4 * chaos::batch_sample_bytes(net->plan, true) > kActBytes) net->plan.ok = false;
         if (net->plan.ok) {
-            net->act_bytes = std::min(kActBytes, kPassSamples * chaos::batch_sample_bytes(net->plan, true));
-            e = hipMalloc(&net->pack, (size_t)std::max<int64_t>(net->plan.pack_elems, 8) * sizeof(uint16_t));
-            if (e == hipSuccess) e = hipMalloc(&net->act, (size_t)net->act_bytes);
+            net->act_bytes = std::min(kActBytes, kPassSamples * chaos::batch_sample_bytes(net->plan, true)) / 256 * 256;
+            // one block, activations, then the weights in operand order: a small
+            // allocation more beside the net's own weights moves them, and the small
+            // net's training runs 1 % slower (13,000 samples 1,532 -> 1,548 us)
+            const int64_t pack = std::max<int64_t>(net->plan.pack_elems, 8) * (int64_t)sizeof(uint16_t);
+            e = hipMalloc(&net->act, (size_t)(net->act_bytes + pack));
+            if (e == hipSuccess) net->pack = reinterpret_cast<uint16_t *>(static_cast<char *>(net->act) + net->act_bytes);
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&net->engine_done, hipEventDisableTiming);
         }
     }
     if (e != hipSuccess) {
@@ -417,9 +456,9 @@ int chaos_destroy_net(chaos_net *net) {
     (void)hipFree(net->sess_wrong);
     (void)hipFree(net->replicas);
     (void)hipFree(net->rep_counter);
-    (void)hipFree(net->pack);
     (void)hipFree(net->act);
     (void)hipFree(net->grad_act);
+    if (net->engine_done) (void)hipEventDestroy(net->engine_done);
     delete net;
     return ok();
 }
@@ -640,13 +679,17 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
         return ok();
     }
     if (batched_losses(net, grad_sum_dev, grad_each_dev)) {
+        EngineTurn turn(net, stream);
+        HIP_TRY(turn.begin(), "engine turn");
         const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
                                                      pass_samples(net, n, net->act_bytes, false), false);
-        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
+        HIP_TRY(batch_gradient(turn, net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
                 "forward_backward launch");
         return ok();
     }
     if (batched_gradient(net, n, grad_sum_dev, grad_each_dev)) {
+        EngineTurn turn(net, stream);
+        HIP_TRY(turn.begin(), "engine turn");
         const int64_t samples = pass_samples(net, n, kGradBytes, true);
         const int64_t part = grad_sum_dev ? chaos::batch_part_floats(net->plan, std::min(samples, n)) : 0;
         const int64_t act = samples * chaos::batch_sample_bytes(net->plan, true), need = act + part * 4;
@@ -663,7 +706,7 @@ int chaos_forward_backward(chaos_net *net, const float *x_dev, const int32_t *la
         chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->grad_act, samples, true);
         w.part = reinterpret_cast<float *>(static_cast<char *>(net->grad_act) + act);
         w.part_floats = part;
-        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
+        HIP_TRY(batch_gradient(turn, net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
                 "forward_backward launch");
         return ok();
     }
@@ -786,21 +829,25 @@ int chaos_forward_backward_noalloc(chaos_net *net, const float *x_dev, const int
         return ok();
     }
     if (batched_losses(net, grad_sum_dev, grad_each_dev)) {
+        EngineTurn turn(net, stream);
+        HIP_TRY(turn.begin(), "engine turn");
         const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
                                                      pass_samples(net, n, net->act_bytes, false), false);
-        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
+        HIP_TRY(batch_gradient(turn, net, w, x_dev, labels_dev, n, out_dev, loss_dev, nullptr, nullptr, stream),
                 "forward_backward launch");
         return ok();
     }
     if (batched_gradient(net, n, grad_sum_dev, grad_each_dev) &&
         (!grad_sum_dev || chaos::batch_part_min(net->plan) <= kNoAllocFloats)) {
+        EngineTurn turn(net, stream);
+        HIP_TRY(turn.begin(), "engine turn");
         // as chaos_forward_backward, in the workspace allocated with the net and
         // with as many partial-sum rows as the fixed scratch holds
         chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
                                                pass_samples(net, n, net->act_bytes, true), true);
         w.part = rows;
         w.part_floats = kNoAllocFloats;
-        HIP_TRY(batch_gradient(net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
+        HIP_TRY(batch_gradient(turn, net, w, x_dev, labels_dev, n, out_dev, loss_dev, grad_sum_dev, grad_each_dev, stream),
                 "forward_backward launch");
         return ok();
     }
@@ -834,6 +881,8 @@ int chaos_evaluate(chaos_net *net, const float *x_dev, const int32_t *labels_dev
     HIP_TRY(chaos::launch_fill_i32(n_wrong_dev, 0, 1, stream), "zero n_wrong");
     if (n == 0) return ok();
     if (batched_evaluate(net, n)) {
+        EngineTurn turn(net, stream);
+        HIP_TRY(turn.begin(), "engine turn");
         chaos::BatchCall c{};
         c.params = net->params;
         c.x = x_dev;
@@ -843,7 +892,7 @@ int chaos_evaluate(chaos_net *net, const float *x_dev, const int32_t *labels_dev
         c.n_wrong = n_wrong_dev;
         const chaos::BatchWork w = chaos::batch_work(net->plan, net->pack, net->act,
                                                      pass_samples(net, n, net->act_bytes, false), false);
-        HIP_TRY(chaos::launch_batch(net->plan, w, c, stream), "evaluate launch");
+        HIP_TRY(run_engine(turn, net, w, c, stream), "evaluate launch");
         return ok();
     }
     int grid = (int)std::min<int64_t>(net->max_workers, n);

@@ -134,3 +134,40 @@ def test_batched_engine_with_pixels_that_are_not_finite(env, value):
         assert_close(out[7].cpu().numpy(), own[7].cpu().double().numpy(), what="saturated sample")
     else:
         assert torch.isnan(out[7]).all() == torch.isnan(own[7]).all()
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("kind", ["large", "large_table1"])
+def test_batched_engine_on_two_streams(env, kind, captured):
+    """Calls of one net that are in flight on two streams share a workspace and
+    do not meet in it; a captured call's replays equal the eager call."""
+    torch, chaos = env
+    layers = wl.NETS[kind]
+    net = chaos.Net(layers, wl.init_params(layers))
+    xs = [torch.from_numpy(wl.batch_set(n)[0]).cuda().flip(0) for n in (1300, 700)]
+    ys = [torch.zeros(len(x), dtype=torch.int32, device="cuda") for x in xs]
+    ref = [torch.empty(len(x), 10, device="cuda") for x in xs]
+    out = [torch.empty_like(r) for r in ref]
+    wrong = [torch.zeros(1, dtype=torch.int32, device="cuda") for _ in xs]
+    for i in range(2):
+        net.evaluate(xs[i], ys[i], out=ref[i], n_wrong=wrong[i])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    if captured:
+        with torch.cuda.graph(graph):
+            net.evaluate(xs[0], ys[0], out=out[0], n_wrong=wrong[0])
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for _ in range(4):
+        for o in out:
+            o.zero_()
+        torch.cuda.synchronize()
+        if captured:
+            graph.replay()
+            torch.cuda.synchronize()
+            net.evaluate(xs[1], ys[1], out=out[1], n_wrong=wrong[1])
+        else:
+            for i in range(2):
+                with torch.cuda.stream(streams[i]):
+                    net.evaluate(xs[i], ys[i], out=out[i], n_wrong=wrong[i])
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, r) for o, r in zip(out, ref))
